@@ -172,6 +172,14 @@ int lqcd_dslash_dagger(const lqcd_geom_t *g, void *out, const void *in, const vo
                        const void *U, double alpha, double beta, int prec, int link,
                        void *stream);
 
+/* lqcd_dslash / lqcd_dslash_dagger (dagger != 0) with the result as a
+   canonical spinor array of canon_prec reals instead of an internal field:
+   what lqcd_unpack_spinor would make of it, without the pass over memory.
+   prec F64 or F32.  out_canon must not alias in or y. */
+int lqcd_dslash_canonical(const lqcd_geom_t *g, void *out_canon, int canon_prec, const void *in,
+                          const void *y, const void *U, double alpha, double beta, int dagger,
+                          int prec, int link, void *stream);
+
 /* Even-odd blocks: out_e = alpha * D_eo in_o + beta * y_e (lqcd_meo) and
    out_o = alpha * D_oe in_e + beta * y_o (lqcd_moe); dagger != 0 applies the
    corresponding block of D_hop^dag, i.e. (D_oe)^dag for meo and (D_eo)^dag
@@ -334,6 +342,14 @@ int lqcd_cg_solve(const lqcd_geom_t *g, void *x_e, const void *b_e,
 int lqcd_fermion_force(const lqcd_geom_t *g, void *F_out, const void *X, const void *Y,
                        const void *U, double coeff, int mode, int accumulate,
                        int prec, int link, void *stream);
+
+/* lqcd_fermion_force with the result as a canonical link array of canon_prec
+   reals instead of an internal field, what lqcd_unpack_gauge would make of
+   it.  F_add: an internal LINK18 field of precision prec that is added to the
+   result, or NULL. */
+int lqcd_fermion_force_canonical(const lqcd_geom_t *g, void *out_canon, int canon_prec,
+                                 const void *F_add, const void *X, const void *Y, const void *U,
+                                 double coeff, int mode, int prec, int link, void *stream);
 
 /* ---------------------------------------------------------------------- */
 /* shifts and lattice SU(3) products (the paper's building blocks)          */

@@ -55,6 +55,8 @@ SIGNATURES = {
                             c_int, c_int, c_void_p]),
     "lqcd_dslash_dagger": (c_int, [G, c_void_p, c_void_p, c_void_p, c_void_p, c_double, c_double,
                                    c_int, c_int, c_void_p]),
+    "lqcd_dslash_canonical": (c_int, [G, c_void_p, c_int, c_void_p, c_void_p, c_void_p, c_double,
+                                      c_double, c_int, c_int, c_int, c_void_p]),
     "lqcd_meo": (c_int, [G, c_void_p, c_void_p, c_void_p, c_void_p, c_double, c_double, c_int,
                          c_int, c_int, c_void_p]),
     "lqcd_moe": (c_int, [G, c_void_p, c_void_p, c_void_p, c_void_p, c_double, c_double, c_int,
@@ -81,6 +83,8 @@ SIGNATURES = {
                               ctypes.POINTER(CGStatsT), c_void_p]),
     "lqcd_fermion_force": (c_int, [G, c_void_p, c_void_p, c_void_p, c_void_p, c_double, c_int,
                                    c_int, c_int, c_int, c_void_p]),
+    "lqcd_fermion_force_canonical": (c_int, [G, c_void_p, c_int, c_void_p, c_void_p, c_void_p,
+                                             c_void_p, c_double, c_int, c_int, c_int, c_void_p]),
     "lqcd_cshift": (c_int, [G, c_void_p, c_void_p, c_int, c_int, c_int, c_void_p]),
     "lqcd_colour_mul": (c_int, [G, c_void_p, c_void_p, c_void_p, c_int, c_int, c_int, c_int,
                                 c_void_p]),

@@ -29,11 +29,9 @@ class WilsonMatrix(torch.autograd.Function):
             raise ValueError("link_grad is 'raw' or 'su3'")
         Uf = L.pack_gauge(lattice, U.contiguous(), prec, link)
         pf = L.pack_spinor(lattice, psi.contiguous(), prec, L.FULL)
-        of = L.new_spinor(lattice, prec, L.FULL, psi.device, zero=False)
-        L.wilson(of, pf, Uf, kappa)
         ctx.save_for_backward(psi, U)
         ctx.cfg = (kappa, lattice, prec, link, link_grad)
-        return L.unpack_spinor(of, dtype=psi.dtype)
+        return L.wilson_canonical(pf, Uf, kappa, psi.dtype)
 
     @staticmethod
     def backward(ctx, g):
@@ -43,17 +41,14 @@ class WilsonMatrix(torch.autograd.Function):
         gf = L.pack_spinor(lattice, g.contiguous().to(psi.dtype), prec, L.FULL)
         gpsi = gU = None
         if ctx.needs_input_grad[0]:
-            of = L.new_spinor(lattice, prec, L.FULL, psi.device, zero=False)
-            L.wilson(of, gf, Uf, kappa, dagger=True)
-            gpsi = L.unpack_spinor(of, dtype=psi.dtype)
+            gpsi = L.wilson_canonical(gf, Uf, kappa, psi.dtype, dagger=True)
         if ctx.needs_input_grad[1]:
             pf = L.pack_spinor(lattice, psi.contiguous(), prec, L.FULL)
             if link_grad == "su3":
                 mode = 0
             else:
                 mode = 2 if link == L.LINK12 else 1
-            F = L.fermion_force(pf, gf, Uf, -kappa, mode=mode)
-            gU = L.unpack_gauge(F, dtype=U.dtype)
+            gU = L.fermion_force_canonical(pf, gf, Uf, -kappa, mode, U.dtype)
         return gpsi, gU, None, None, None, None, None
 
 
@@ -119,9 +114,8 @@ class NormalSolve(torch.autograd.Function):
                 return f
 
             G = L.fermion_force(x_field(lam), y_field(x), U_hi, kappa * kappa, mode=1)
-            L.fermion_force(x_field(x), y_field(lam), U_hi, kappa * kappa, mode=1, out=G,
-                            accumulate=True)
-            gU = L.unpack_gauge(G, dtype=U.dtype)
+            gU = L.fermion_force_canonical(x_field(x), y_field(lam), U_hi, kappa * kappa, 1, U.dtype,
+                                           add=G)
         return gb, gU, None, None, None, None, None
 
 

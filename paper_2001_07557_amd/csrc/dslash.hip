@@ -11,6 +11,8 @@
 // lane owns one site and neighbours are plain indexed loads, so no lane
 // permutation exists.
 
+#include <type_traits>
+
 #include "lqcd_internal.h"
 #include "reduce.h"
 #include "hop_common.h"
@@ -87,6 +89,26 @@ namespace lqcd {
 #endif
 constexpr int64_t INFINITY_CACHE_BYTES = (int64_t)256 << 20;
 
+// acc = alpha acc + beta y.  The fused product is spelled out, so that every
+// instance rounds alike (the compiler may fuse either one).
+template <int P, bool HASY>
+__device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
+                                            cplx<typename real_of<P>::type> acc[12]) {
+    using T = typename real_of<P>::type;
+    const T alpha = (T)a.alpha;
+    if constexpr (HASY) {
+        cplx<T> y[12];
+        load_spinor<P>(a.y[p], s, y);
+        const T beta = (T)a.beta;
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+            acc[k] = {fmad(alpha, acc[k].re, beta * y[k].re), fmad(alpha, acc[k].im, beta * y[k].im)};
+    } else {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc[k] = scale(alpha, acc[k]);
+    }
+}
+
 // Epilogue shared by the kernel shapes: out = alpha acc + beta y; NORM = 1
 // also returns |out|^2 of the site; NORM = 2 (the solver's last hop, with a y
 // term) stores nothing of out = A p but updates the CG iterate in place,
@@ -96,18 +118,7 @@ template <int P, bool HASY, int NORM, bool NT>
 __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t s,
                                                cplx<typename real_of<P>::type> acc[12]) {
     using T = typename real_of<P>::type;
-    const T alpha = (T)a.alpha;
-    if constexpr (HASY) {
-        cplx<T> y[12];
-        load_spinor<P>(a.y[p], s, y);
-        const T beta = (T)a.beta;
-#pragma unroll
-        for (int k = 0; k < 12; ++k)
-            acc[k] = {alpha * acc[k].re + beta * y[k].re, alpha * acc[k].im + beta * y[k].im};
-    } else {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[k] = scale(alpha, acc[k]);
-    }
+    hop_combine<P, HASY>(a, p, s, acc);
     if constexpr (NORM == 2 && P == LQCD_F64 && !LQCD_LAYOUT_AOS) {
         // FP64: four words of p, x and r at a time, so that the three
         // vectors are never live together (occupancy of the 4-way shape)
@@ -166,6 +177,31 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t 
     return nrm;
 }
 
+// Canonical output (CT: its real type): wave 0 stages the tile's sites in LDS
+// the staging of the hops no longer needs, and the whole block writes them.
+// Every thread of the block calls it.  The extra barrier and LDS pass cost 8 us
+// of an 88 us launch (24^4, FP64) and save the 24 us (and 130 MB) of a
+// separate unpacking pass.
+template <typename CT, int P, bool HASY, int THREADS>
+__device__ __forceinline__ void hop_canon(const HopArgs &a, int p, int64_t s, bool mine,
+                                          cplx<typename real_of<P>::type> acc[12], v4u *stage) {
+    constexpr int GS = spinor_granules<CT>();
+    const int lane = threadIdx.x & 63;
+    if (mine) {
+        hop_combine<P, HASY>(a, p, s, acc);
+        // the reads of the staged hops come before these writes of another type
+        asm volatile("" ::: "memory");
+        CT *d = reinterpret_cast<CT *>(stage + lane * (GS + 1));
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            d[2 * k] = (CT)acc[k].re;
+            d[2 * k + 1] = (CT)acc[k].im;
+        }
+    }
+    __syncthreads();
+    canon_store<GS, THREADS>(a.g, reinterpret_cast<v4u *>(a.out[0]), p, s - lane, stage);
+}
+
 // The five fields read first lie on the five 64-byte lines of the arguments.
 static_assert(offsetof(HopArgs, cg_x) <= 5 * 64 && sizeof(HopArgs) <= 6 * 64,
               "the fields read first span five lines, the CG-update fields a sixth");
@@ -198,11 +234,12 @@ __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, in
 }
 
 // 4-way shape: wave w computes both hops of direction w; waves 1..3 leave
-// their partial spinors in LDS and wave 0 adds them up.
-template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO>
+// their partial spinors in LDS and wave 0 adds them up.  CT: real type of a
+// canonical output, void for the internal layout.
+template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO, typename CT = void>
 __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
-    __shared__ cplx<T> part[3][12][64];
+    __shared__ alignas(16) cplx<T> part[3][12][64];
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     int p;
@@ -235,7 +272,11 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[j][k][lane];
-        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+        if constexpr (std::is_void<CT>::value) nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+    }
+    if constexpr (!std::is_void<CT>::value) {
+        static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(part), "the tile fits the staging");
+        hop_canon<CT, P, HASY, 256>(a, p, s, w == 0 && active, acc, reinterpret_cast<v4u *>(part));
     }
     if constexpr (NORM) {
         // wave 0 holds every site of the tile: a wave reduction suffices and
@@ -462,10 +503,10 @@ __device__ __forceinline__ void rebuild_row(const HopArgs &a, int p, int64_t s,
 // 8-way shape: wave w computes hop w (direction w/2, forward for even w) and
 // stages the two colour vectors of its multiplied half-spinor in LDS; wave 0
 // rebuilds the four spin rows from the eight staged half-spinors.
-template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool ROWS, bool HALO>
+template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool ROWS, bool HALO, typename CT = void>
 __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
-    __shared__ cplx<T> chi[8][6][64];
+    __shared__ alignas(16) cplx<T> chi[8][6][64];
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     int p;
@@ -509,8 +550,8 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         return;
     }
     double nrm[1] = {0.0};
+    cplx<T> acc[12];
     if (w == 0 && active) {
-        cplx<T> acc[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = {0, 0};
         add_staged<0, P, DAG>(chi, lane, acc);
@@ -521,7 +562,11 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         add_staged<5, P, DAG>(chi, lane, acc);
         add_staged<6, P, DAG>(chi, lane, acc);
         add_staged<7, P, DAG>(chi, lane, acc);
-        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+        if constexpr (std::is_void<CT>::value) nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+    }
+    if constexpr (!std::is_void<CT>::value) {
+        static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(chi), "the tile fits the staging");
+        hop_canon<CT, P, HASY, 512>(a, p, s, w == 0 && active, acc, reinterpret_cast<v4u *>(chi));
     }
     if constexpr (NORM) {
         // wave 0 holds every site of the tile: a wave reduction suffices and
@@ -605,8 +650,34 @@ static void launch_p(const HopArgs &a, bool hasy, int norm, dim3 grid, hipStream
     }
 }
 
+// Canonical output (FP64 and FP32 storage, both parities): links and stores
+// without hints, as a both-parity launch wants them.
+template <int P, int LK, bool DAG, bool HASY, typename CT>
+static void launch_canon_ct(const HopArgs &a, dim3 grid, hipStream_t st) {
+    if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, 0, 0, false, false, CT><<<grid, 512, 0, st>>>(a);
+    else hop4_kernel<P, LK, DAG, HASY, 0, 0, false, CT><<<grid, 256, a.lds_extra, st>>>(a);
+}
+
+template <int P, int LK, bool DAG>
+static void launch_canon(const HopArgs &a, bool hasy, dim3 grid, hipStream_t st) {
+    if (a.canon == 8) {
+        if (hasy) launch_canon_ct<P, LK, DAG, true, double>(a, grid, st);
+        else launch_canon_ct<P, LK, DAG, false, double>(a, grid, st);
+    } else {
+        if (hasy) launch_canon_ct<P, LK, DAG, true, float>(a, grid, st);
+        else launch_canon_ct<P, LK, DAG, false, float>(a, grid, st);
+    }
+}
+
 template <int P, int LK>
 static void launch_l(const HopArgs &a, bool dag, bool hasy, int norm, dim3 grid, hipStream_t st) {
+    if constexpr (P != LQCD_F16) {
+        if (a.canon != 0) {
+            if (dag) launch_canon<P, LK, true>(a, hasy, grid, st);
+            else launch_canon<P, LK, false>(a, hasy, grid, st);
+            return;
+        }
+    }
     if (dag) launch_p<P, LK, true>(a, hasy, norm, grid, st);
     else launch_p<P, LK, false>(a, hasy, norm, grid, st);
 }
@@ -698,7 +769,8 @@ static int validate_hop(const lqcd_geom_t *gg, Geom *g, const void *out, const v
 }
 
 static int full_hop(const lqcd_geom_t *gg, void *out, const void *in, const void *y, const void *U,
-                    double alpha, double beta, int prec, int link, bool dag, void *stream) {
+                    double alpha, double beta, int prec, int link, bool dag, void *stream,
+                    int canon_real = 0) {
     Geom g;
     int rc = validate_hop(gg, &g, out, in, U, prec, link);
     if (rc) return rc;
@@ -710,6 +782,7 @@ static int full_hop(const lqcd_geom_t *gg, void *out, const void *in, const void
     a.alpha = alpha;
     a.beta = beta;
     a.par0 = 0;
+    a.canon = canon_real;
     // output parity p reads the other parity's half of the input
     a.out[0] = (char *)out;
     a.out[1] = (char *)out + hb;
@@ -731,6 +804,16 @@ extern "C" int lqcd_dslash_dagger(const lqcd_geom_t *g, void *out, const void *i
                                   const void *y, const void *U, double alpha, double beta,
                                   int prec, int link, void *stream) {
     return full_hop(g, out, in, y, U, alpha, beta, prec, link, true, stream);
+}
+
+extern "C" int lqcd_dslash_canonical(const lqcd_geom_t *g, void *out_canon, int canon_prec,
+                                     const void *in, const void *y, const void *U, double alpha,
+                                     double beta, int dagger, int prec, int link, void *stream) {
+    if (canon_prec != LQCD_F64 && canon_prec != LQCD_F32) return LQCD_EINVAL;
+    if (prec != LQCD_F64 && prec != LQCD_F32) return LQCD_EINVAL;
+    if (out_canon == y) return LQCD_EINVAL;  // (out_canon == NULL is refused either way)
+    return full_hop(g, out_canon, in, y, U, alpha, beta, prec, link, dagger != 0, stream,
+                    canon_prec == LQCD_F64 ? 8 : 4);
 }
 
 static int eo_hop(const lqcd_geom_t *gg, int out_par, void *out, const void *in, const void *y,

@@ -150,6 +150,9 @@ struct HopArgs {
     uint32_t lds_extra;
     // t-march launches: t-slices per block (0: one tile per block)
     int tseg;
+    // host side: out[0] is a canonical array of reals of this many bytes (8
+    // or 4; both-parity launches, FP64 and FP32 storage); 0: internal layout
+    int canon;
 };
 
 // Tile visited by logical block b (within one parity).  With bricks of bz

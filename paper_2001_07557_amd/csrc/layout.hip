@@ -66,20 +66,8 @@ bool make_geom(const lqcd_geom_t *g, Geom *out) {
 // 28 -> 26, out 34 -> 24 (5.4 TB/s); FP32 at 16^4: 8.2 -> 7.8, 15.7 -> 9.1,
 // 4.7 -> 4.4, 5.9 -> 4.4.
 
-// Parity of y + z + t of the row of checkerboard site s (Ly and Lz are even,
-// so the parities of y, z and t are those of the three quotients).
-__device__ __forceinline__ int row_parity(const Geom &g, uint32_t s) {
-    const uint32_t r1 = fdiv(s, g.dx);
-    const uint32_t r2 = fdiv(r1, g.dy);
-    return (int)((r1 ^ r2 ^ fdiv(r2, g.dz)) & 1);
-}
-
 constexpr int SPINOR_BLOCK = 128;  // sites per block: 64 pairs, or 128 sites of one parity
 constexpr int GAUGE_PAIRS = 32;    // pairs per block, one thread per link
-
-// 16-byte granules of one canonical site
-template <typename CT> constexpr int spinor_granules() { return 24 * (int)sizeof(CT) / WORD; }
-template <typename CT> constexpr int gauge_granules() { return 72 * (int)sizeof(CT) / WORD; }
 
 // One block of a spinor conversion: the pairs (HALF: the sites of parity
 // `par`) s0, s0 + 1, ... as LDS slots, and this thread's own site.

@@ -502,6 +502,46 @@ __device__ __forceinline__ Coord cb_coords(const Geom &g, int p, int64_t s) {
     return c;
 }
 
+// Parity of y + z + t of the row of checkerboard site s (Ly and Lz are even,
+// so the parities of y, z and t are those of the three quotients).  The
+// canonical pair 2s, 2s + 1 holds site s of both parities, parity p at
+// 2s + (p ^ row parity).
+__device__ __forceinline__ int row_parity(const Geom &g, uint32_t s) {
+    const uint32_t r1 = fdiv(s, g.dx);
+    const uint32_t r2 = fdiv(r1, g.dy);
+    return (int)((r1 ^ r2 ^ fdiv(r2, g.dz)) & 1);
+}
+
+// 16-byte granules of one site of a canonical array
+template <typename CT> constexpr int spinor_granules() { return 24 * (int)sizeof(CT) / WORD; }
+template <typename CT> constexpr int gauge_granules() { return 72 * (int)sizeof(CT) / WORD; }
+
+// A tile's results on their way to a canonical array: site `lane` of the tile
+// stands in LDS GS + 1 granules after the one before it (odd: lanes writing
+// one granule each hit different banks).
+template <int GS> constexpr int canon_stage_bytes() { return TILE * (GS + 1) * WORD; }
+
+// The staged sites of tile s0 / 64 of parity p, written by the THREADS
+// threads of a block: a site is one contiguous canonical run of GS granules,
+// at every other site of the array (the other parity's tile, the next block
+// on the same XCD, fills the rest, so the stores are plain and meet in the
+// L2).
+template <int GS, int THREADS>
+__device__ __forceinline__ void canon_store(const Geom &g, v4u *__restrict__ dst, int p, int64_t s0,
+                                            const v4u *stage) {
+    const int64_t left = g.vh - s0;
+    const int n = (int)(left < TILE ? left : TILE) * GS;
+#pragma unroll
+    for (int j = 0; j < (TILE * GS + THREADS - 1) / THREADS; ++j) {
+        const int i = j * THREADS + (int)threadIdx.x;
+        if (i < n) {
+            const int l = i / GS, c = i % GS;
+            const int64_t lex = 2 * (s0 + l) + (p ^ row_parity(g, (uint32_t)(s0 + l)));
+            dst[lex * GS + c] = stage[l * (GS + 1) + c];
+        }
+    }
+}
+
 // Logical block index for an XCD-aware launch: the hardware hands
 // consecutive workgroups to the 8 XCDs in turn, so block b runs on XCD b % 8;
 // renumbering gives every XCD one contiguous range of tiles (its own L2 then

@@ -239,6 +239,25 @@ def wilson(out: SpinorField, inp: SpinorField, U: GaugeField, kappa: float, dagg
     return dslash(out, inp, U, -kappa, 1.0, inp, dagger)
 
 
+def wilson_canonical(inp: SpinorField, U: GaugeField, kappa: float, dtype,
+                     dagger: bool = False) -> torch.Tensor:
+    """M inp (M^dag if dagger) as a canonical tensor: unpack_spinor of
+    :func:`wilson`, written by the operator kernel itself (FP64 and FP32
+    storage; binary16 results are rounded to storage first)."""
+    _same(inp, U)
+    lat = inp.lattice
+    if U.prec == F16:
+        out = new_spinor(lat, U.prec, FULL, inp.buf.device, zero=False)
+        return unpack_spinor(wilson(out, inp, U, kappa, dagger), dtype=dtype)
+    if inp.subset != FULL:
+        raise RuntimeError("dslash works on full fields")
+    res = torch.empty(lat.spinor_shape(), dtype=dtype, device=inp.buf.device)
+    _check(_lib.load().lqcd_dslash_canonical(lat.ref(), _ptr(res), _canon_prec(res), inp.ptr, inp.ptr,
+                                             U.ptr, -kappa, 1.0, int(dagger), U.prec, U.link,
+                                             _stream()), "dslash_canonical")
+    return res
+
+
 def meo(out: SpinorField, inp: SpinorField, U: GaugeField, alpha: float = 1.0, beta: float = 0.0,
         y: Optional[SpinorField] = None, dagger: bool = False):
     """out_e = alpha * D_eo inp_o + beta * y_e (block of D_hop^dag if dagger)."""
@@ -399,6 +418,19 @@ def fermion_force(X: SpinorField, Y: SpinorField, U: GaugeField, coeff: float, m
     _check(_lib.load().lqcd_fermion_force(lat.ref(), out.ptr, X.ptr, Y.ptr, U.ptr, coeff, mode,
                                           int(accumulate), U.prec, U.link, _stream()),
            "fermion_force")
+    return out
+
+
+def fermion_force_canonical(X: SpinorField, Y: SpinorField, U: GaugeField, coeff: float, mode: int,
+                            dtype, add: Optional[GaugeField] = None) -> torch.Tensor:
+    """unpack_gauge of :func:`fermion_force` (plus the field `add`), written
+    by the force kernel itself."""
+    _same(X, Y, U, add)
+    lat = X.lattice
+    out = torch.empty(lat.links_shape(), dtype=dtype, device=X.buf.device)
+    _check(_lib.load().lqcd_fermion_force_canonical(
+        lat.ref(), _ptr(out), _canon_prec(out), add.ptr if add is not None else None, X.ptr, Y.ptr,
+        U.ptr, coeff, mode, U.prec, U.link, _stream()), "fermion_force_canonical")
     return out
 
 

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2001_07557_amd as P
+from paper_2001_07557_amd import lqcd as L
 from tests.gpu_helpers import dev, host
 
 pytestmark = pytest.mark.gpu
@@ -102,3 +103,31 @@ def test_gauge_layout_bits(dims, prec, link, dtype):
     if link == 18:
         back = host(P.unpack_gauge(f, dtype=dev(U).dtype))
         assert np.array_equal(back, U.astype(np.complex64).astype(dtype) if prec == P.F32 else U)
+
+
+# ragged and whole tiles, and the smallest lattice of the blocked tile order
+OUT_DIMS = [(2, 2, 2, 2), (6, 4, 2, 6), (22, 6, 4, 2), (8, 8, 8, 8), (16, 16, 16, 64)]
+
+
+@pytest.mark.parametrize("dims", OUT_DIMS)
+@pytest.mark.parametrize("prec,link", [(P.F64, 18), (P.F64, 12), (P.F32, 18), (P.F32, 12)])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_canonical_results_equal_unpacked_ones(dims, prec, link, dtype):
+    """The operator and the link gradient written as canonical arrays by
+    their own kernels: the bits of the internal result, unpacked."""
+    lat = P.Lattice(dims, (-1, 1, 1, -1))
+    rng = np.random.default_rng(7)
+    U = P.pack_gauge(lat, dev(draw(rng, lat.links_shape(), np.complex128)), prec, link)
+    x, y = (P.pack_spinor(lat, dev(draw(rng, lat.spinor_shape(), np.complex128)), prec) for _ in range(2))
+    out = P.new_spinor(lat, prec, P.FULL)
+    for dagger in (False, True):
+        want = P.unpack_spinor(P.wilson(out, x, U, 0.11, dagger), dtype=dtype)
+        assert torch.equal(L.wilson_canonical(x, U, 0.11, dtype, dagger), want)
+    add = P.fermion_force(y, x, U, 0.3, mode=1)
+    for mode in (0, 1) + ((2,) if link == 12 else ()):
+        want = P.unpack_gauge(P.fermion_force(x, y, U, 0.7, mode=mode), dtype=dtype)
+        assert torch.equal(L.fermion_force_canonical(x, y, U, 0.7, mode, dtype), want)
+        both = P.new_gauge(lat, prec, P.LINK18)
+        both.buf.copy_(add.buf)
+        want = P.unpack_gauge(P.fermion_force(x, y, U, 0.7, mode=mode, out=both, accumulate=True), dtype=dtype)
+        assert torch.equal(L.fermion_force_canonical(x, y, U, 0.7, mode, dtype, add=add), want)
