@@ -12,7 +12,9 @@ backward pass runs two library kernels:
   su(3)-projected force F = TA(G U^dag) for U -> exp(eps T) U
   (``link_grad="su3"``).
 
-Only psi and U are saved for backward; phi is not kept.
+psi and U are saved for backward together with their packed fields, which the
+backward kernels read as they are (the packed psi only where dL/dU is wanted);
+phi is not kept.
 """
 
 from __future__ import annotations
@@ -29,21 +31,22 @@ class WilsonMatrix(torch.autograd.Function):
             raise ValueError("link_grad is 'raw' or 'su3'")
         Uf = L.pack_gauge(lattice, U.contiguous(), prec, link)
         pf = L.pack_spinor(lattice, psi.contiguous(), prec, L.FULL)
-        ctx.save_for_backward(psi, U)
+        # psi and U themselves carry the check that nobody has changed them
+        ctx.save_for_backward(psi, U, Uf.buf, pf.buf if ctx.needs_input_grad[1] else None)
         ctx.cfg = (kappa, lattice, prec, link, link_grad)
         return L.wilson_canonical(pf, Uf, kappa, psi.dtype)
 
     @staticmethod
     def backward(ctx, g):
-        psi, U = ctx.saved_tensors
+        psi, U, u_buf, psi_buf = ctx.saved_tensors
         kappa, lattice, prec, link, link_grad = ctx.cfg
-        Uf = L.pack_gauge(lattice, U.contiguous(), prec, link)
+        Uf = L.GaugeField(lattice, prec, link, u_buf)
         gf = L.pack_spinor(lattice, g.contiguous().to(psi.dtype), prec, L.FULL)
         gpsi = gU = None
         if ctx.needs_input_grad[0]:
             gpsi = L.wilson_canonical(gf, Uf, kappa, psi.dtype, dagger=True)
         if ctx.needs_input_grad[1]:
-            pf = L.pack_spinor(lattice, psi.contiguous(), prec, L.FULL)
+            pf = L.SpinorField(lattice, prec, L.FULL, psi_buf)
             if link_grad == "su3":
                 mode = 0
             else:

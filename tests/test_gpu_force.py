@@ -349,3 +349,35 @@ def test_normal_solve_gradcheck_2x4():
     tU = dev(U).requires_grad_(True)
     f = lambda bb, uu: P.normal_solve(bb, uu, KAPPA, lat, P.F64, P.LINK18, tol=1e-13)  # noqa: E731
     assert torch.autograd.gradcheck(f, (tb, tU), eps=1e-5, atol=1e-6, rtol=1e-5)
+
+
+@pytest.mark.parametrize("wants", [(True, False), (False, True), (True, True)])
+def test_autograd_saved_fields(wants):
+    """The backward pass reads the fields packed by the forward pass: each
+    combination of wanted gradients gives the bits of the full one, through
+    saved-tensor hooks too, and a change of psi or U in between is refused."""
+    dims = (6, 4, 2, 6)
+    lat = P.Lattice(dims)
+    U, psi = LI.workload_fields(36, dims)
+    g = dev(LI.gaussian_spinor(np.random.default_rng(37), dims))
+
+    def run(wants):
+        a = dev(psi).requires_grad_(wants[0])
+        b = dev(U).requires_grad_(wants[1])
+        return a, b, P.wilson_matrix(a, b, KAPPA, lat, P.F64, P.LINK12)
+
+    a, b, phi = run((True, True))
+    phi.backward(g)
+    full = (a.grad, b.grad)
+    with torch.autograd.graph.save_on_cpu():
+        a, b, phi = run(wants)
+    phi.backward(g, retain_graph=True)
+    phi.backward(g)
+    for got, want, asked in zip((a.grad, b.grad), full, wants):
+        assert (got is None) if not asked else torch.equal(got, 2 * want)
+    for which in (0, 1):
+        a, b, phi = run(wants)
+        with torch.no_grad():
+            (a, b)[which].mul_(2)
+        with pytest.raises(RuntimeError):
+            phi.backward(g)
