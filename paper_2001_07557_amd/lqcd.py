@@ -44,7 +44,9 @@ def _check(rc: int, where: str):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without a torch.cuda.Stream object around
+    # it: the object alone took 2.5 us of a 7.7 us call on the smallest lattice
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
