@@ -87,6 +87,21 @@ namespace lqcd {
 #ifndef LQCD_HOP_TMARCH_MIN_LOG2
 #define LQCD_HOP_TMARCH_MIN_LOG2 17
 #endif
+// Whole-lattice even-odd launches with odd output walk every XCD's range of
+// tiles backwards.  Operators alternate output parities (Mhat, its adjoint,
+// the solver's four hops), and a hop that starts where the one before it
+// ended finds the last links and spinors of that one in the Infinity Cache;
+// walked the same way round, a working set beyond 256 MB has evicted what the
+// next launch reads first.  Mhat, three field sets in turn (us, same way ->
+// back and forth, two runs each): 32^4 FP32-12 113.0-113.5 -> 108.5, FP64-12
+// 227.9-228.7 -> 226.6, FP64-18 285.4 -> 284.8; 48^3x96 FP32-12 1172 -> 1151,
+// 48^4 FP64-18 1583 -> 1562.  Loading the links of the last 48-200 MB of a
+// launch plainly, to keep more of them, gained another 1-3% at 24^3x48 and
+// lost 1.5% at 48^3x96 (twice the code), so the link hint stays per launch.
+// 0 switches it off (ablation).
+#ifndef LQCD_HOP_ZIGZAG
+#define LQCD_HOP_ZIGZAG 1
+#endif
 constexpr int64_t INFINITY_CACHE_BYTES = (int64_t)256 << 20;
 
 // acc = alpha acc + beta y.  The fused product is spelled out, so that every
@@ -224,7 +239,7 @@ __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, in
     asm volatile("" ::"s"(a.bpp), "s"(a.g.lxh), "s"(a.g.vh), "s"(a.in[0]), "s"(a.stream));
 #endif
     const uint32_t bx = blockIdx.x;
-    blk = LQCD_HOP_XCD ? xcd_block(bx, a.nblk) : (int64_t)bx;
+    blk = LQCD_HOP_XCD ? xcd_block(bx, a.nblk, a.rev) : (int64_t)bx;
     // paired: blocks 2i / 2i + 1 take the even / odd tile i; otherwise the
     // first bpp blocks take parity par0 and the rest the other parity
     const int q = blk >= a.bpp ? 1 : 0;
@@ -721,6 +736,7 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
                                                                                : LQCD_HOP_F64_LDS_MIN_LOG2))
                       ? (uint32_t)LQCD_HOP_F64_LDS_EXTRA
                       : 0u;
+    a.rev = LQCD_HOP_ZIGZAG && nparity == 1 && region < 0 && a.par0 == LQCD_ODD;
     dim3 grid((unsigned)(a.bpp * nparity));
     // t-march launches (4-way shape, one parity, whole lattice, whole tiles
     // per t-slice in a multiple of 8 columns): one block per column and

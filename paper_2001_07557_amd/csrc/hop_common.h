@@ -133,6 +133,7 @@ struct HopArgs {
     double alpha, beta;
     double *partial;      // optional per-block |out|^2
     int stream;           // non-temporal hints: bit 0 output stores, bit 1 link loads
+    int rev;              // walk each XCD's range of tiles backwards
     int rows;             // 8-way shape: waves 0-3 rebuild one spin row each
     // boundary-slice launches: the t-hops that cross the t boundary read
     // face[0] (projected half-spinors of the forward neighbours) and face[1]

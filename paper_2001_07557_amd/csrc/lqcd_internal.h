@@ -545,12 +545,14 @@ __device__ __forceinline__ void canon_store(const Geom &g, v4u *__restrict__ dst
 // Logical block index for an XCD-aware launch: the hardware hands
 // consecutive workgroups to the 8 XCDs in turn, so block b runs on XCD b % 8;
 // renumbering gives every XCD one contiguous range of tiles (its own L2 then
-// sees the neighbouring sites of its range).  A bijection for any nblocks.
-__device__ __forceinline__ int64_t xcd_block(uint32_t b, uint32_t nblocks) {
+// sees the neighbouring sites of its range), walked backwards if `rev`.  A
+// bijection for any nblocks.
+__device__ __forceinline__ int64_t xcd_block(uint32_t b, uint32_t nblocks, int rev = 0) {
     constexpr uint32_t NX = 8;
     const uint32_t q = nblocks / NX, r = nblocks % NX;
     const uint32_t x = b % NX, k = b / NX;
-    return (int64_t)(x * q + (x < r ? x : r) + k);
+    const uint32_t n = q + (x < r ? 1 : 0);  // blocks of this XCD
+    return (int64_t)(x * q + (x < r ? x : r) + (rev ? n - 1 - k : k));
 }
 
 // HIP error bookkeeping shared by the entry points.
