@@ -245,7 +245,11 @@ __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, in
     const int q = blk >= a.bpp ? 1 : 0;
     const uint32_t lb = (uint32_t)(a.paired ? blk >> 1 : blk - q * a.bpp);
     p = a.paired ? (int)(blk & 1) : a.par0 ^ q;
-    return brick_tile(a, lb) * HOP_SITES + lane;
+    const int64_t tile = brick_tile(a, lb);
+    // the partial of a tile in slab order, whose blocks outnumber the tiles,
+    // goes by the tile
+    if (a.brick.lz == 0) blk = tile;
+    return tile * HOP_SITES + lane;
 }
 
 // 4-way shape: wave w computes both hops of direction w; waves 1..3 leave
@@ -298,7 +302,7 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         // the other waves leave after the staging barrier
         if (w == 0) {
             const double t = wave_sum(nrm[0]);
-            if (lane == 0) a.partial[blk] = t;
+            if (lane == 0 && blk < a.g.ntiles) a.partial[blk] = t;
         }
     }
 }
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
     }
     if constexpr (NORM) {
         const double t = wave_sum(nrm[0]);
-        if (lane == 0) a.partial[blk] = t;
+        if (lane == 0 && blk < a.g.ntiles) a.partial[blk] = t;
     }
 }
 
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         // the other waves leave after the staging barrier
         if (w == 0) {
             const double t = wave_sum(nrm[0]);
-            if (lane == 0) a.partial[blk] = t;
+            if (lane == 0 && blk < a.g.ntiles) a.partial[blk] = t;
         }
     }
 }
@@ -702,10 +706,10 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     if (prec == LQCD_F16 && a0.g.ntiles > F16_MAX_TILES) return LQCD_EINVAL;
     HopArgs a = a0;
     if (region < 0) {
-        a.bpp = (a.g.vh + HOP_SITES - 1) / HOP_SITES;
-        a.brick = make_brick(a.g, brick_plan(a.g, prec,
-                                             nparity == 2 && LQCD_HOP_PAIRED ? 2
-                                             : nparity == 1 && LQCD_BRICK_BAND_EO ? 1 : 0));
+        a.brick = launch_brick(a.g, prec, nparity == 2 && LQCD_HOP_PAIRED ? 2
+                                          : nparity == 1 && LQCD_BRICK_BAND_EO ? 1 : 0,
+                               nparity == 2);
+        a.bpp = brick_blocks(a.g, a.brick);
         a.face[0] = a.face[1] = nullptr;
     } else {
         // interior slices 1 .. Lt-2, or boundary slices 0 and Lt-1

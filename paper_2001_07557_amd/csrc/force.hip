@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void force_k(ForceArgs a) {
     const int w = threadIdx.x >> 6;
     const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
     const int p = (int)(blk & 1);
-    const int64_t s = brick_order((uint32_t)(blk >> 1), a.brick) * 64 + lane;
+    const int64_t s = brick_order((uint32_t)(blk >> 1), a.brick, a.g) * 64 + lane;
     const bool active = s < a.g.vh;
     if (active) {
         // wave q stages spin rows 2(q & 1) and 2(q & 1) + 1 of X (q < 2) or Y
@@ -360,8 +360,8 @@ static int force_entry(const lqcd_geom_t *gg, void *F, void *canon, int canon_pr
     a.coeff = coeff;
     a.mode = mode;
     a.accumulate = accumulate ? 1 : 0;
-    a.bpp = (g.vh + 63) / 64;
-    a.brick = make_brick(g, brick_plan(g, prec));
+    a.brick = launch_brick(g, prec, 0, true);
+    a.bpp = LQCD_FORCE_STAGE || canon ? brick_blocks(g, a.brick) : g.ntiles;
     dim3 grid((unsigned)(2 * a.bpp));
     hipStream_t st = (hipStream_t)stream;
     if (prec == LQCD_F64) {

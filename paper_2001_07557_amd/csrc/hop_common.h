@@ -102,10 +102,30 @@ __device__ __forceinline__ void hop_fence(cplx<T> acc[N]) {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// Slab order.  Where no group of z-planes is a whole number of tiles (18x18
+// planes of 162 sites, 28x28, 26x26, ...) every t-slice is cut into eight runs
+// of consecutive sites of equal length (slabs of Lz/8 planes, a fraction of a
+// plane included), and a tile belongs to the slice and slab of its first
+// site.  Slab j of slice t is then the run of tiles [slab_tile(j),
+// slab_tile(j + 1)), at most one longer in one slice than in another, so
+// every XCD gets one slab, padded to the same number of tiles per slice, and
+// walks it in t order as the bricks are walked; the blocks of a pad get the
+// tile after the last one and find no site there.
+// Measured (us, plain order -> slabs, two runs each within 0.5%): Mhat 28^4
+// FP32-12 75.8 -> 68.8, 30^4 FP32-18 124.1 -> 112.7, 46^3x50 FP32-12 587 ->
+// 546, binary16 319 -> 300; full-lattice M 28^4 FP64-18 160.3 -> 142.7,
+// 46^3x50 FP64-18 1379 -> 1159, 18^2x42x40 FP64-12 121.1 -> 116.  Slabs half
+// as thick, two per XCD, lose 5-8% (the planes at every edge are read again).
+__host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t, uint32_t j) {
+    return (t * (uint32_t)g.st + (uint32_t)(j * g.st >> 3) + (TILE - 1)) >> TILE_SHIFT;
+}
+
 // Cache-blocked tile order: tiles per z-group, z-groups per brick, Lt and
 // z-groups in Lz.  The plain order is the same formula with pt = bz = lz = 1
 // and lt larger than any tile index, so the traversal needs no branch on the
 // mode.
+// lz = 0 marks the slab order (below), where pt is the most tiles a slab has
+// in one slice.
 struct Brick {
     FastDiv pt, bz, lt;
     int lz;
@@ -161,7 +181,7 @@ struct HopArgs {
 // the three t-slices of a brick that one output slice touches stay in the
 // XCD's L2, where the plain order would revisit each input slice from memory
 // for the t-neighbours of the slices before and after it.
-__device__ __forceinline__ int64_t brick_order(uint32_t b, const Brick &k) {
+__host__ __device__ __forceinline__ int64_t brick_order(uint32_t b, const Brick &k, const Geom &g) {
     const uint32_t r1 = fdiv(b, k.pt);    // (z-group, t) in traversal order
     const uint32_t r2 = fdiv(r1, k.bz);   // (brick, band, t)
     const uint32_t r3 = fdiv(r2, k.lt);   // (brick, band)
@@ -170,11 +190,16 @@ __device__ __forceinline__ int64_t brick_order(uint32_t b, const Brick &k) {
     const uint32_t zi = r1 - r2 * k.bz.d;
     const uint32_t t = k.t0 + (r2 - r3 * k.lt.d) * k.tstep;
     const uint32_t band = r3 - zc * k.nyb.d;
+    if (k.lz == 0) {
+        // (bz = nyb = 1: zc is the slab)
+        const uint32_t at = slab_tile(g, t, zc) + tile;
+        return at < slab_tile(g, t, zc + 1) ? (int64_t)at : g.ntiles;
+    }
     return (int64_t)((t * k.lz + zc * k.bz.d + zi) * k.ptg + band * k.pt.d + tile);
 }
 
 __device__ __forceinline__ int64_t brick_tile(const HopArgs &a, uint32_t b) {
-    return brick_order(b, a.brick);
+    return brick_order(b, a.brick, a.g);
 }
 
 // Blocked traversal plan: the tiles of a z-group (the fewest consecutive
@@ -254,6 +279,46 @@ inline Brick make_brick(const Geom &g, const BrickPlan &b) {
     k.t0 = 0;
     k.tstep = 1;
     return k;
+}
+
+// Slab order for lattices that the blocked order does not cover, from V/2 >=
+// 2^LQCD_BRICK_MIN_LOG2 sites as the bricks and where a slab of a slice is at
+// least eight tiles (the pad stays small).  A slab thinner than 1.5 planes
+// (Lz < 12) reads so many planes at its edges twice that an even-odd launch
+// is better off without: Mhat FP32-12 38^2x14x40 99.6 -> 90.7 us, 30^2x10x60
+// 62.8 -> 64.8, 46^2x6x60 87.8 -> 91.2.  Launches over both parities take it
+// at any Lz: M 30^2x10x60 FP64-12 115.5 -> 107.8, 46^2x6x60 FP64-18 192.6 ->
+// 188.5.
+#ifndef LQCD_HOP_SLABS
+#define LQCD_HOP_SLABS 1
+#endif
+inline bool use_slabs(const Geom &g, const BrickPlan &b, bool both) {
+    return LQCD_HOP_SLABS && b.bz == 0 && g.vh >= ((int64_t)1 << LQCD_BRICK_MIN_LOG2) &&
+           g.st >= 8 * 8 * TILE && (both || g.L[2] >= 12);
+}
+
+inline Brick make_slab_brick(const Geom &g) {
+    Brick k = make_brick(g, BrickPlan{0, 0, 0});
+    uint32_t most = 1;
+    for (uint32_t t = 0; t < (uint32_t)g.L[3]; ++t)
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t n = slab_tile(g, t, j + 1) - slab_tile(g, t, j);
+            if (n > most) most = n;
+        }
+    k.pt = make_fastdiv(most);
+    k.ptg = most;
+    k.lz = 0;
+    k.lt = make_fastdiv((uint32_t)g.L[3]);
+    return k;
+}
+
+// The traversal of a whole-lattice launch, and its blocks per parity.
+inline Brick launch_brick(const Geom &g, int prec, int halves, bool both) {
+    const BrickPlan p = brick_plan(g, prec, halves);
+    return use_slabs(g, p, both) ? make_slab_brick(g) : make_brick(g, p);
+}
+inline int64_t brick_blocks(const Geom &g, const Brick &k) {
+    return k.lz == 0 ? (int64_t)8 * k.lt.d * k.pt.d : g.ntiles;
 }
 
 // Traversal of the t-slices t0, t0 + tstep, ... (nt of them) only, each a
