@@ -50,31 +50,32 @@ namespace lqcd {
 #ifndef LQCD_HOP_PAIRED
 #define LQCD_HOP_PAIRED 1
 #endif
-// Blocks in flight of the FP64 4-way kernel on large lattices.  With ~120
-// VGPRs four blocks fit a CU, so an XCD's 32 CUs keep 128 tiles in flight,
-// more than one t-slice of its z-slab, and the three input t-slices the
-// brick order relies on no longer fit its 4 MB L2 beside them.  From
-// V/2 >= 2^20 sites (48^3x96 and up) the launch adds LQCD_HOP_F64_LDS_EXTRA
-// bytes of dynamic LDS per block (36 + 18 KB: two blocks per CU).  Measured
-// in two sessions (fraction of 8 TB/s, four -> two blocks per CU): 48^3x96
-// FP64-18 68.6 -> 70.7 and 68.6 -> 69.5, FP64-12 65.6 -> 67.7 and 65.5 ->
-// 67.1, full-lattice FP64-18 M 4.39 -> 4.88 TB/s; at 32^4 FP64-18 78.4 ->
-// 79.8 and 78.3 -> 77.9, FP64-12 73.9 -> 72.7 and 73.8 -> 73.0 (not taken);
-// three blocks per CU +0.6 at 48^3x96, one block 57%; binary16 storage
-// (also 4-way) loses 8 points with it and keeps four.  A both-parity launch
-// (full-lattice D_hop and M) keeps two tiles' links and both halves of psi
-// in play and takes the limit from V/2 >= 2^17: full-lattice FP64-18 M at
-// 24^4 4.82 -> 5.15 TB/s and at 32^4 4.67-4.73 -> 4.74-4.91 TB/s (two runs
-// each).  LQCD_HOP_EXTRA_LDS forces a value for every 4-way launch
-// (ablations).
-#ifndef LQCD_HOP_F64_LDS_EXTRA
-#define LQCD_HOP_F64_LDS_EXTRA 18432
-#endif
+// Blocks in flight of the FP64 4-way kernel.  With ~120 VGPRs and 36 KB of
+// LDS four blocks fit a CU, and an XCD's 32 CUs then keep 128 tiles in flight,
+// more than one t-slice of its z-slab: the three input t-slices the brick
+// order relies on no longer fit its 4 MB L2 beside them.  Even-odd launches
+// from V/2 >= 2^17 and both-parity launches from 2^15 add dynamic LDS that
+// leaves three blocks per CU.  Measured (us, four -> three -> two blocks per
+// CU): full-lattice M 24^4 FP64-18 81.4 -> 78.5 -> 80.6, FP64-12 67.8 -> 67.1
+// -> 71.2; 32^4 FP64-18 238.5 -> 228.7 -> 236.5, FP64-12 196.2 -> 193.4 ->
+// 209.5; 48^3x96 FP64-18 2470 -> 2397 -> 2445, FP64-12 2016 -> 1996 -> 2156;
+// 16^3x32 FP64-18 33.8 -> 32.6; Mhat 32^4 FP64-18 285.1 -> 283.7, 28^4
+// FP64-18 175.6 -> 173.5, 38^3x40 FP64-12 -> 512 -> 527, 48^3x96 FP64-12
+// -> 2489 -> 2526, but 16^3x32 FP64-12 27.7 -> 29.4 (below the line).  The
+// launches that want two blocks are both-parity 18-real ones in plain order
+// (38^2x14x40 -> 214 -> 210) or in slab order where the three t-slices of both
+// halves (144 bytes per site of a t-slice and slab) overflow the L2: 38^3x40
+// 575 -> 536 -> 522, 46^3x50 1318 -> 1221 -> 1180; at 28^4 (1.6 MB) three are
+// ahead, 147.0 -> 140.5 -> 144.4.
+// binary16 storage (also 4-way) loses 8 points with two and keeps what fits.
+// LQCD_HOP_EXTRA_LDS forces a value for every 4-way launch (ablations).
+constexpr uint32_t F64_LDS_THREE = 6144, F64_LDS_TWO = 18432;
+constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #ifndef LQCD_HOP_F64_LDS_MIN_LOG2
-#define LQCD_HOP_F64_LDS_MIN_LOG2 20
+#define LQCD_HOP_F64_LDS_MIN_LOG2 17
 #endif
 #ifndef LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2
-#define LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2 17
+#define LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2 15
 #endif
 #ifndef LQCD_HOP_EXTRA_LDS
 #define LQCD_HOP_EXTRA_LDS -1
@@ -735,11 +736,14 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     // backward from the paired tile), so it keeps them cached
     const bool link_nt = LQCD_LINK_NT && !a.paired && spinors + links > INFINITY_CACHE_BYTES;
     a.stream = LQCD_HOP_STREAM >= 0 ? LQCD_HOP_STREAM : (out_nt ? 1 : 0) | (link_nt ? 2 : 0);
-    a.lds_extra = LQCD_HOP_EXTRA_LDS >= 0 ? (uint32_t)LQCD_HOP_EXTRA_LDS
-                  : prec == LQCD_F64 && a.g.vh >= ((int64_t)1 << (a.paired ? LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2
-                                                                               : LQCD_HOP_F64_LDS_MIN_LOG2))
-                      ? (uint32_t)LQCD_HOP_F64_LDS_EXTRA
-                      : 0u;
+    a.lds_extra = LQCD_HOP_EXTRA_LDS >= 0 ? (uint32_t)LQCD_HOP_EXTRA_LDS : 0u;
+    if (LQCD_HOP_EXTRA_LDS < 0 && prec == LQCD_F64 &&
+        a.g.vh >= ((int64_t)1 << (a.paired ? LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2 : LQCD_HOP_F64_LDS_MIN_LOG2))) {
+        const bool plain = a.brick.lz == 1 && a.g.vh >= ((int64_t)1 << LQCD_BRICK_MIN_LOG2);
+        const bool wide = a.brick.lz == 0 && a.g.st * (2 * 3 * 192 / 8) > F64_SLAB_TWO_BYTES;
+        const bool two = a.paired && link == 18 && (plain || wide);
+        a.lds_extra = two ? F64_LDS_TWO : F64_LDS_THREE;
+    }
     a.rev = LQCD_HOP_ZIGZAG && nparity == 1 && region < 0 && a.par0 == LQCD_ODD;
     dim3 grid((unsigned)(a.bpp * nparity));
     // t-march launches (4-way shape, one parity, whole lattice, whole tiles
