@@ -10,10 +10,16 @@
 // iterations, and every iteration once the decay so far says the tolerance
 // is near, so the solve stops at the first iteration that reaches it.
 //
-// Per iteration: 4 hop kernels (the second also produces |Mhat p|^2 = <p, A p>
-// block partials; the fourth does x += a p, r -= a Ap and the |r|^2 partials
-// in its epilogue, so Ap is never stored), p = r + b p, and two single-block
-// kernels that finish the sums and form alpha, beta.
+// Per iteration five launches: the direction update (x += a p, p = r + b p;
+// its blocks finish the |r|^2 sum and form beta themselves), four hops (the
+// second leaves the |Mhat p|^2 = <p, A p> block partials, the third sums runs
+// of them on the side, the fourth forms alpha from those, does r -= a A p in
+// its epilogue, so A p is never stored, and leaves the |r|^2 partials).
+// Kernel times per iteration (us, trace; seven launches before, with two
+// one-block scalar kernels and x updated in the fourth hop): 32^4 binary16
+// inner 26 + 30 + 26 + 43 + 12.5 + 2 x 4.9 -> 26 + 30 + 26 + 35 + 23, 24^3x48
+// FP32 29 + 34 + 29 + 53 + 15 + 2 x 4.8 -> 30 + 34 + 29 + 40 + 26 (the
+// direction update moves 159 MB, 6.1 TB/s).
 
 #include <chrono>
 #include <cmath>
@@ -43,80 +49,115 @@ constexpr double DELTA_F32 = 1e-3;
 // a few iterations later.
 constexpr double INNER_MARGIN2 = 0.25;
 
-enum { S_RR = 0, S_PAP, S_ALPHA, S_RROLD, S_BETA, S_OUT, S_COUNT = 16 };
-enum { OP_ALPHA = 0, OP_RRNEW, OP_RESET, OP_SUM, OP_SETRR };
-
-// Fixed-order sum of the block partials followed by the scalar recurrence.
-// One block; thread t adds entries t, t + B, t + 2B, ... in four interleaved
-// chains so that four loads are in flight (one chain per thread left the
-// 8192 hop partials of a 32^4 solve at 15 us, a third of a hop launch).
-constexpr int SCALAR_BLOCK = 512;
-template <int OP>
-__global__ __launch_bounds__(SCALAR_BLOCK) void cg_scalar_k(const double *partial, int64_t n,
-                                                            int stride, double *sc) {
-    const int64_t B = blockDim.x;
+// Fixed-order sum of n partials, `stride` apart, by a block of SUM_BLOCK
+// threads: thread t adds entries t, t + B, t + 2B, ... in four interleaved
+// chains, so that four loads are in flight.  Valid in every thread.
+constexpr int SUM_BLOCK = 512;
+__device__ __forceinline__ double partial_total(const double *partial, int n, int stride) {
+    constexpr int B = SUM_BLOCK;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int64_t i = threadIdx.x;
+    int i = threadIdx.x;
     for (; i + 3 * B < n; i += 4 * B) {
-        a0 += partial[i * stride];
-        a1 += partial[(i + B) * stride];
-        a2 += partial[(i + 2 * B) * stride];
-        a3 += partial[(i + 3 * B) * stride];
+        a0 += partial[(int64_t)i * stride];
+        a1 += partial[(int64_t)(i + B) * stride];
+        a2 += partial[(int64_t)(i + 2 * B) * stride];
+        a3 += partial[(int64_t)(i + 3 * B) * stride];
     }
-    for (; i < n; i += B) a0 += partial[i * stride];
+    for (; i < n; i += B) a0 += partial[(int64_t)i * stride];
     double v[1] = {(a0 + a1) + (a2 + a3)};
     block_sum<1>(v);
+    __shared__ double total;
+    if (threadIdx.x == 0) total = v[0];
+    __syncthreads();
+    return total;
+}
+
+// The sum for the host.  RESID: the sum of a recomputed residual, after which
+// x has no step pending.
+template <bool RESID>
+__global__ __launch_bounds__(SUM_BLOCK) void cg_sum_k(const double *partial, int n, int stride, double *sc) {
+    const double s = partial_total(partial, n, stride);
     if (threadIdx.x == 0) {
-        const double s = v[0];
-        if constexpr (OP == OP_ALPHA) {
-            // <p, A p> = 0 only when p = 0: the iteration has terminated
-            // exactly (e.g. a source spanned by few eigenvectors); take no step
-            // and let the next residual check confirm convergence.
-            sc[S_PAP] = s;
-            sc[S_ALPHA] = s > 0.0 ? sc[S_RR] / s : 0.0;
-        } else if constexpr (OP == OP_RRNEW || OP == OP_RESET) {
-            // RRNEW: rr_old <- rr before the update; RESET keeps rr_old of the
-            // iteration and replaces rr by the norm of the recomputed residual
-            if constexpr (OP == OP_RRNEW) sc[S_RROLD] = sc[S_RR];
-            sc[S_RR] = s;
-            sc[S_BETA] = sc[S_RROLD] > 0.0 ? s / sc[S_RROLD] : 0.0;
-        } else if constexpr (OP == OP_SETRR) {
-            sc[S_RR] = s;
-        } else {
-            sc[S_OUT] = s;
+        sc[CG_OUT] = s;
+        if (RESID) sc[CG_ALPHA] = 0.0;
+    }
+}
+
+// Sums of CG_GROUPS runs of n partials.
+__global__ __launch_bounds__(64) void cg_groups_k(const double *partial, int n, double *groups) {
+    const int per = (n + CG_GROUPS - 1) / CG_GROUPS, lo = (int)blockIdx.x * per;
+    const double t = wave_total(partial + lo, n - lo < per ? n - lo : per);
+    if (threadIdx.x == 0) groups[blockIdx.x] = t;
+}
+
+// x += alpha p, p = rs + beta p.  Every block sums the n partials of |rs|^2
+// (few blocks, each over several sites per thread) and forms beta = |rs|^2 /
+// |rs before|^2; the first iteration finds 0 there and takes p = rs.
+constexpr int DIR_BLOCKS = 512;
+// partials beyond which they are summed into groups by a launch of their own
+constexpr int CG_MANY = 16384;
+// partials that every block of the last hop sums itself: 512 of them (16^4)
+// take a wave eight loads, while summing groups in the hop before, where all
+// of its blocks run at once, put 0.9 us on a 5.2 us launch
+constexpr int CG_FEW = 1024;
+template <int P>
+__global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char *rs, char *xs, double *sc,
+                                                            const double *partial, int n, int stride,
+                                                            int slot, int64_t vh) {
+    using T = typename real_of<P>::type;
+    const int64_t step = (int64_t)gridDim.x * SUM_BLOCK;
+    int64_t s = (int64_t)blockIdx.x * SUM_BLOCK + threadIdx.x;
+    cplx<T> vr[12], vp[12], vx[12];
+    // the first site's words arrive while the partials are summed
+    if (s < vh) {
+        load_spinor<P>(rs, s, vr);
+        load_spinor<P>(p, s, vp);
+        load_spinor<P>(xs, s, vx);
+    }
+    const double old = sc[CG_RR + (slot ^ 1)];
+    const T alpha = (T)sc[CG_ALPHA];
+    const double rr = partial_total(partial, n, stride);
+    const double b = old > 0.0 ? rr / old : 0.0;
+    const T beta = (T)b;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[CG_RR + slot] = rr;
+        sc[CG_BETA] = b;
+    }
+    while (s < vh) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            vx[k] = {fmad(alpha, vp[k].re, vx[k].re), fmad(alpha, vp[k].im, vx[k].im)};
+            vp[k] = {fmad(beta, vp[k].re, vr[k].re), fmad(beta, vp[k].im, vr[k].im)};
+        }
+        store_spinor<P>(xs, s, vx);
+        store_spinor<P>(p, s, vp);
+        s += step;
+        if (s < vh) {
+            load_spinor<P>(rs, s, vr);
+            load_spinor<P>(p, s, vp);
+            load_spinor<P>(xs, s, vx);
         }
     }
 }
 
-// p = rs + beta p.
+// x64 += xs + alpha p (inner precision; the step of the last iteration is
+// still pending), xs = 0.
 template <int P>
-__global__ __launch_bounds__(CG_BLOCK) void cg_direction_k(char *p, const char *rs, const double *sc,
-                                                           int64_t vh) {
+__global__ __launch_bounds__(CG_BLOCK) void cg_fold_k(char *x64, char *xs, const char *p, const double *sc,
+                                                      int64_t vh) {
     using T = typename real_of<P>::type;
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= vh) return;
-    const T beta = (T)sc[S_BETA];
-    cplx<T> vr[12], vp[12];
-    load_spinor<P>(rs, s, vr);
-    load_spinor<P>(p, s, vp);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) vp[k] = {vr[k].re + beta * vp[k].re, vr[k].im + beta * vp[k].im};
-    store_spinor<P>(p, s, vp);
-}
-
-// x64 += xs (inner precision), xs = 0.
-template <int P>
-__global__ __launch_bounds__(CG_BLOCK) void cg_fold_k(char *x64, char *xs, int64_t vh) {
-    using T = typename real_of<P>::type;
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= vh) return;
+    const T alpha = (T)sc[CG_ALPHA];
     cplx<double> vx[12];
-    cplx<T> v[12];
+    cplx<T> v[12], vp[12];
     load_spinor<LQCD_F64>(x64, s, vx);
     load_spinor<P>(xs, s, v);
+    load_spinor<P>(p, s, vp);
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-        vx[k] = {vx[k].re + (double)v[k].re, vx[k].im + (double)v[k].im};
+        vx[k] = {vx[k].re + (double)fmad(alpha, vp[k].re, v[k].re),
+                 vx[k].im + (double)fmad(alpha, vp[k].im, v[k].im)};
         v[k] = {0, 0};
     }
     store_spinor<LQCD_F64>(x64, s, vx);
@@ -152,7 +193,8 @@ __global__ __launch_bounds__(CG_BLOCK) void cg_residual_k(char *r, const char *b
 struct CGWork {
     char *xs, *rs, *p, *te, *to;      // inner precision
     char *r64, *te64, *to64;          // FP64
-    double *partial;
+    double *partial;                  // of |r|^2 (and of the FP64 sums)
+    double *pap, *groups;             // of <p, A p>, in te64 (idle meanwhile)
     double *sc;
     size_t bytes;
 };
@@ -186,7 +228,10 @@ static CGWork cg_layout(const Geom &g, int prec, char *base) {
     w.te64 = take(hb64);
     w.to64 = take(hb64);
     w.partial = (double *)take(sizeof(double) * cg_partials(g));
-    w.sc = (double *)take(sizeof(double) * S_COUNT);
+    w.sc = (double *)take(sizeof(double) * CG_SCALARS);
+    // hop_partials(g, 1) + CG_GROUPS numbers, of the 1536 doubles per tile
+    w.groups = (double *)w.te64;
+    w.pap = base ? w.groups + CG_GROUPS : nullptr;
     w.bytes = off;
     return w;
 }
@@ -233,14 +278,20 @@ struct Solver {
     int link64;
     const char *U64;
     CGWork w;
+    int n_rr, stride_rr;  // the |rs|^2 partials in w.partial
 
     int hop(int out_par, char *out, const char *in, const char *y, double alpha, bool dag, int pr,
-            int lk, const char *U_, double *partial, char *cg_x = nullptr,
-            const char *cg_p = nullptr) {
+            int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0) {
         HopArgs a{};
-        a.cg_x = cg_x;
-        a.cg_p = cg_p;
-        a.cg_alpha = w.sc + S_ALPHA;
+        a.cg = cg;
+        a.slot = slot;
+        a.sc = w.sc;
+        a.groups = w.groups;
+        const int n = (int)hop_partials(g, 1);
+        const int per = (n + CG_GROUPS - 1) / CG_GROUPS;
+        a.n_groups = (n + per - 1) / per;
+        a.sums = cg == CG_PRE || n <= CG_FEW ? w.pap : w.groups;
+        a.n_sums = cg == CG_PRE || n <= CG_FEW ? n : a.n_groups;
         a.g = g;
         a.U = U_;
         a.alpha = alpha;
@@ -253,20 +304,31 @@ struct Solver {
         return hop_launch(a, pr, lk, dag, 1, st);
     }
 
-    // One inner iteration's operator and update: te = Mhat p (with the
-    // <p, A p> = |Mhat p|^2 partials, summed into alpha), then
-    // Mhat^dag te = A p formed inside the last hop, which updates xs and rs
-    // and leaves the |rs|^2 partials.
-    int apply_a_update(int pr, int lk, const char *U_) {
+    // One inner iteration: the direction update from the |rs|^2 partials of
+    // the step before, te = Mhat p with the <p, A p> = |Mhat p|^2 partials,
+    // then Mhat^dag te = A p formed inside the last hop, which updates rs and
+    // leaves its |rs|^2 partials.
+    template <int P>
+    int iterate(int slot) {
         const double k2 = -kappa * kappa;
-        int rc = hop(LQCD_ODD, w.to, w.p, nullptr, 1.0, false, pr, lk, U_, nullptr);
-        if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p, k2, false, pr, lk, U_, w.partial);
-        if (!rc) {
-            cg_scalar_k<OP_ALPHA><<<1, SCALAR_BLOCK, 0, st>>>(w.partial, hop_partials(g, 1), 1, w.sc);
-            rc = check_launch();
+        const double *sums = w.partial;
+        int n = n_rr, stride = stride_rr;
+        if (n > CG_MANY) {
+            cg_groups_k<<<CG_GROUPS, 64, 0, st>>>(w.partial, n, w.groups);
+            sums = w.groups;
+            n = CG_GROUPS;
         }
-        if (!rc) rc = hop(LQCD_ODD, w.to, w.te, nullptr, 1.0, true, pr, lk, U_, nullptr);
-        if (!rc) rc = hop(LQCD_EVEN, w.rs, w.to, w.te, k2, true, pr, lk, U_, w.partial, w.xs, w.p);
+        const int64_t blocks = (g.vh + SUM_BLOCK - 1) / SUM_BLOCK;
+        cg_direction_k<P><<<dim3((unsigned)(blocks < DIR_BLOCKS ? blocks : DIR_BLOCKS)), SUM_BLOCK, 0, st>>>(
+            w.p, w.rs, w.xs, w.sc, sums, n, stride, slot, g.vh);
+        int rc = check_launch();
+        if (!rc) rc = hop(LQCD_ODD, w.to, w.p, nullptr, 1.0, false, P, link, U, nullptr);
+        if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p, k2, false, P, link, U, w.pap);
+        if (!rc) rc = hop(LQCD_ODD, w.to, w.te, nullptr, 1.0, true, P, link, U, nullptr,
+                          hop_partials(g, 1) > CG_FEW ? CG_PRE : CG_NONE);
+        if (!rc) rc = hop(LQCD_EVEN, w.rs, w.to, w.te, k2, true, P, link, U, w.partial, CG_UPDATE, slot);
+        n_rr = (int)hop_partials(g, 1);
+        stride_rr = 1;
         return rc;
     }
 
@@ -294,12 +356,19 @@ struct Solver {
         return LQCD_OK;
     }
 
-    // |v|^2 of an FP64 or inner-precision half field into scalar slot via OP
-    template <int OP>
-    int norm_into(const char *v, int pr) {
+    // the block partials of |v|^2 of an FP64 or inner-precision half field
+    int norm_partials(const char *v, int pr) {
         launch_reduce(g, 1, v, nullptr, pr, w.partial, st);
-        cg_scalar_k<OP><<<1, SCALAR_BLOCK, 0, st>>>(w.partial, reduce_blocks(g, 1), 2, w.sc);
+        n_rr = (int)reduce_blocks(g, 1);
+        stride_rr = 2;
         return check_launch();
+    }
+
+    // their sum on the host
+    int total(double *host) {
+        cg_sum_k<false><<<1, SUM_BLOCK, 0, st>>>(w.partial, n_rr, stride_rr, w.sc);
+        const int rc = check_launch();
+        return rc ? rc : read(host, CG_OUT);
     }
 
     // r64 = b - A64 x64; returns |r64|^2 on the host
@@ -307,10 +376,10 @@ struct Solver {
         int rc = apply_a(LQCD_F64, link64, U64, x64, w.r64, w.te64, w.to64, nullptr);
         if (rc) return rc;
         cg_residual_k<<<grid(), CG_BLOCK, 0, st>>>(w.r64, b, g.vh, w.partial);
-        cg_scalar_k<OP_SUM><<<1, SCALAR_BLOCK, 0, st>>>(w.partial, nblk(), 1, w.sc);
+        cg_sum_k<true><<<1, SUM_BLOCK, 0, st>>>(w.partial, (int)nblk(), 1, w.sc);
         rc = check_launch();
         if (rc) return rc;
-        return read(rr, S_OUT);
+        return read(rr, CG_OUT);
     }
 
     template <int P>
@@ -319,8 +388,8 @@ struct Solver {
         stats->iterations = 0;
         stats->reliable_updates = 0;
         double bb = 0.0;
-        int rc = norm_into<OP_SUM>(b, LQCD_F64);
-        if (!rc) rc = read(&bb, S_OUT);
+        int rc = norm_partials(b, LQCD_F64);
+        if (!rc) rc = total(&bb);
         if (rc) return rc;
         if (!std::isfinite(bb)) return LQCD_ENAN;
         if (bb == 0.0) {
@@ -339,8 +408,8 @@ struct Solver {
         // a zero starting guess (the common case) needs no FP64 operator
         // application: r = b
         double xx = 0.0;
-        rc = norm_into<OP_SUM>(x64, LQCD_F64);
-        if (!rc) rc = read(&xx, S_OUT);
+        rc = norm_partials(x64, LQCD_F64);
+        if (!rc) rc = total(&xx);
         if (rc) return rc;
         if (xx == 0.0) {
             launch_convert(g, 1, w.r64, LQCD_F64, b, LQCD_F64, st);
@@ -355,16 +424,18 @@ struct Solver {
         stats->iterated_residual = stats->true_residual;
         if (rr <= target) return LQCD_OK;
 
-        // inner start: rs = r64, xs = 0, p = rs, rr = |rs|^2
+        // inner start: rs = r64, xs = 0, and p = 0 with beta = alpha = 0 for
+        // the first direction update
         const size_t hb = half_spinor_bytes(g, P);
         hipError_t e = hipMemsetAsync(w.xs, 0, hb, st);
+        if (e == hipSuccess) e = hipMemsetAsync(w.p, 0, hb, st);
+        if (e == hipSuccess) e = hipMemsetAsync(w.sc, 0, sizeof(double) * CG_SCALARS, st);
         if (e != hipSuccess) {
             set_hip_error(e);
             return LQCD_EHIP;
         }
         launch_convert(g, 1, w.rs, P, w.r64, LQCD_F64, st);
-        launch_convert(g, 1, w.p, P, w.rs, P, st);
-        rc = norm_into<OP_SETRR>(w.rs, P);
+        rc = norm_partials(w.rs, P);
         if (rc) return rc;
 
         int k = 0;
@@ -382,15 +453,12 @@ struct Solver {
         double rate = 0.0;
         int next_read = CHECK_EVERY;
         while (true) {
-            rc = apply_a_update(P, link, U);
-            if (rc) return rc;
-            cg_scalar_k<OP_RRNEW><<<1, SCALAR_BLOCK, 0, st>>>(w.partial, hop_partials(g, 1), 1, w.sc);
-            rc = check_launch();
+            rc = iterate<P>(k & 1);
             if (rc) return rc;
             ++k;
             bool reliable = reliable_every > 0 && k % reliable_every == 0;
             if (reliable || k >= next_read || k >= maxiter) {
-                rc = read(&rr_it, S_RR);
+                rc = total(&rr_it);
                 if (rc) return rc;
                 if (!std::isfinite(rr_it)) {
                     stats->iterations = k;
@@ -407,7 +475,7 @@ struct Solver {
                 k_seen = k;
             }
             if (reliable || k >= maxiter) {
-                cg_fold_k<P><<<grid(), CG_BLOCK, 0, st>>>(x64, w.xs, g.vh);
+                cg_fold_k<P><<<grid(), CG_BLOCK, 0, st>>>(x64, w.xs, w.p, w.sc, g.vh);
                 rc = true_residual(x64, b, &rr);
                 if (rc) return rc;
                 stats->reliable_updates += 1;
@@ -420,13 +488,12 @@ struct Solver {
                 rr_ref = rr;
                 // restart the inner residual from the FP64 one, keep p
                 launch_convert(g, 1, w.rs, P, w.r64, LQCD_F64, st);
-                rc = norm_into<OP_RESET>(w.rs, P);
+                rc = norm_partials(w.rs, P);
                 if (rc) return rc;
                 rr_seen = rr;
                 k_seen = k;
                 next_read = k + read_gap(iterations_left(rr, rate, target_inner));
             }
-            cg_direction_k<P><<<grid(), CG_BLOCK, 0, st>>>(w.p, w.rs, w.sc, g.vh);
         }
     }
 };

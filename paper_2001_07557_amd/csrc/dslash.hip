@@ -126,59 +126,27 @@ __device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
 }
 
 // Epilogue shared by the kernel shapes: out = alpha acc + beta y; NORM = 1
-// also returns |out|^2 of the site; NORM = 2 (the solver's last hop, with a y
-// term) stores nothing of out = A p but updates the CG iterate in place,
-// x += c p and r -= c A p (c the device's CG alpha, r at a.out), and returns
-// |r|^2 of the site.
+// also returns |out|^2 of the site; NORM = 2 (CG_UPDATE, with a y term) stores
+// nothing of out = A p but updates r -= cg_alpha A p in place (r at a.out) and
+// returns |r|^2 of the site.  x += alpha p waits for the pass that reads p
+// next anyway (the direction update): one vector less per iteration, and
+// fewer registers here.
 template <int P, bool HASY, int NORM, bool NT>
 __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t s,
-                                               cplx<typename real_of<P>::type> acc[12]) {
+                                               cplx<typename real_of<P>::type> acc[12],
+                                               double cg_alpha = 0.0) {
     using T = typename real_of<P>::type;
     hop_combine<P, HASY>(a, p, s, acc);
-    if constexpr (NORM == 2 && P == LQCD_F64 && !LQCD_LAYOUT_AOS) {
-        // FP64: four words of p, x and r at a time, so that the three
-        // vectors are never live together (occupancy of the 4-way shape)
-        const T c = (T)*a.cg_alpha;
-        const int64_t toff = (s >> TILE_SHIFT) * spinor_tile_bytes(P);
-        const int lane = (int)(s & (TILE - 1));
-        v2d *xw = reinterpret_cast<v2d *>(a.cg_x + toff) + lane;
-        v2d *rw = reinterpret_cast<v2d *>(a.out[p] + toff) + lane;
-        const v2d *pw = reinterpret_cast<const v2d *>(a.cg_p + toff) + lane;
-        T nr = 0;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            cplx<T> vx[4], vr[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int k = 4 * q + j;
-                const v2d dp = pw[k * TILE], dx = xw[k * TILE], dr = rw[k * TILE];
-                vx[j] = {dx.x + c * dp.x, dx.y + c * dp.y};
-                vr[j] = {dr.x - c * acc[k].re, dr.y - c * acc[k].im};
-                nr += norm2(vr[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int k = 4 * q + j;
-                xw[k * TILE] = v2d{vx[j].re, vx[j].im};
-                rw[k * TILE] = v2d{vr[j].re, vr[j].im};
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        return (double)nr;
-    } else if constexpr (NORM == 2) {
-        const T c = (T)*a.cg_alpha;
-        cplx<T> vx[12], vr[12], vp[12];
-        load_spinor<P>(a.cg_p, s, vp);
-        load_spinor<P>(a.cg_x, s, vx);
+    if constexpr (NORM == 2) {
+        const T c = (T)cg_alpha;
+        cplx<T> vr[12];
         load_spinor<P>(a.out[p], s, vr);
         T nr = 0;
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            vx[k] = {vx[k].re + c * vp[k].re, vx[k].im + c * vp[k].im};
             vr[k] = {vr[k].re - c * acc[k].re, vr[k].im - c * acc[k].im};
             nr += norm2(vr[k]);
         }
-        store_spinor<P>(a.cg_x, s, vx);
         store_spinor<P>(a.out[p], s, vr);
         return (double)nr;
     }
@@ -191,6 +159,27 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t 
     }
     store_spinor<P, NT>(a.out[p], s, acc);
     return nrm;
+}
+
+// CG_UPDATE: alpha of this iteration, formed by one wave; block 0 keeps it.
+__device__ __forceinline__ double cg_alpha_of(const HopArgs &a) {
+    const double pap = wave_total(a.sums, a.n_sums);
+    // <p, A p> = 0 only when p = 0: the iteration has terminated exactly
+    // (e.g. a source spanned by few eigenvectors); take no step and let the
+    // next residual check confirm convergence.
+    const double alpha = pap > 0.0 ? a.sc[CG_RR + a.slot] / pap : 0.0;
+    if (blockIdx.x == 0 && (threadIdx.x & 63) == 0) a.sc[CG_ALPHA] = alpha;
+    return alpha;
+}
+
+// CG_PRE: this block's run of the partials, summed by one wave.
+__device__ __forceinline__ void cg_presum(const HopArgs &a) {
+    if (blockIdx.x >= (uint32_t)a.n_groups) return;
+    const int per = (a.n_sums + a.n_groups - 1) / a.n_groups;
+    const int lo = (int)blockIdx.x * per;
+    const int n = a.n_sums - lo < per ? a.n_sums - lo : per;
+    const double t = wave_total(a.sums + lo, n);
+    if ((threadIdx.x & 63) == 0) a.groups[blockIdx.x] = t;
 }
 
 // Canonical output (CT: its real type): wave 0 stages the tile's sites in LDS
@@ -219,8 +208,8 @@ __device__ __forceinline__ void hop_canon(const HopArgs &a, int p, int64_t s, bo
 }
 
 // The five fields read first lie on the five 64-byte lines of the arguments.
-static_assert(offsetof(HopArgs, cg_x) <= 5 * 64 && sizeof(HopArgs) <= 6 * 64,
-              "the fields read first span five lines, the CG-update fields a sixth");
+static_assert(offsetof(HopArgs, sc) <= 5 * 64 && sizeof(HopArgs) <= 7 * 64,
+              "the fields read first span five lines, the solver's the ones after them");
 static_assert(offsetof(HopArgs, bpp) / 64 == 0 &&
                   (offsetof(HopArgs, g) + offsetof(Geom, lxh)) / 64 == 1 &&
                   (offsetof(HopArgs, g) + offsetof(Geom, vh)) / 64 == 2 &&
@@ -256,7 +245,7 @@ __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, in
 // 4-way shape: wave w computes both hops of direction w; waves 1..3 leave
 // their partial spinors in LDS and wave 0 adds them up.  CT: real type of a
 // canonical output, void for the internal layout.
-template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO, typename CT = void>
+template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO, typename CT = void, int CG = CG_NONE>
 __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
     __shared__ alignas(16) cplx<T> part[3][12][64];
@@ -285,6 +274,12 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
 #pragma unroll
         for (int k = 0; k < 12; ++k) part[w - 1][k][lane] = acc[k];
     }
+    __shared__ double alpha;
+    if (NORM == 2 && w == 1) {
+        const double t = cg_alpha_of(a);
+        if (lane == 0) alpha = t;
+    }
+    if (CG == CG_PRE && w == 3) cg_presum(a);
     __syncthreads();
     double nrm[1] = {0.0};
     if (w == 0 && active) {
@@ -292,7 +287,8 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[j][k][lane];
-        if constexpr (std::is_void<CT>::value) nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+        if constexpr (std::is_void<CT>::value)
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(part), "the tile fits the staging");
@@ -414,7 +410,8 @@ __global__ __launch_bounds__(256) void hop4t_kernel(HopArgs a) {
             for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[q][k][lane];
-            const double nrm = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+            const double nrm = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc,
+                                                                           NORM == 2 ? cg_alpha_of(a) : 0.0);
             if constexpr (NORM != 0) {
                 const double tot = wave_sum(nrm);
                 if (lane == 0) a.partial[s >> TILE_SHIFT] = tot;
@@ -452,7 +449,7 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
         hop_direction<3, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, s, c, d, a.face);
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = acc[k] + d[k];
-        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? cg_alpha_of(a) : 0.0);
     }
     if constexpr (NORM) {
         const double t = wave_sum(nrm[0]);
@@ -523,7 +520,8 @@ __device__ __forceinline__ void rebuild_row(const HopArgs &a, int p, int64_t s,
 // 8-way shape: wave w computes hop w (direction w/2, forward for even w) and
 // stages the two colour vectors of its multiplied half-spinor in LDS; wave 0
 // rebuilds the four spin rows from the eight staged half-spinors.
-template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool ROWS, bool HALO, typename CT = void>
+template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool ROWS, bool HALO, typename CT = void,
+          int CG = CG_NONE>
 __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
     __shared__ alignas(16) cplx<T> chi[8][6][64];
@@ -555,6 +553,12 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
             chi[w][3 + k][lane] = x1[k];
         }
     }
+    __shared__ double alpha;
+    if (NORM == 2 && w == 1) {
+        const double t = cg_alpha_of(a);
+        if (lane == 0) alpha = t;
+    }
+    if (CG == CG_PRE && w == 7) cg_presum(a);
     __syncthreads();
     if constexpr (ROWS) {
         static_assert(!HASY && !NORM, "the row-parallel rebuild has no y term and no norm");
@@ -582,7 +586,8 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         add_staged<5, P, DAG>(chi, lane, acc);
         add_staged<6, P, DAG>(chi, lane, acc);
         add_staged<7, P, DAG>(chi, lane, acc);
-        if constexpr (std::is_void<CT>::value) nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc);
+        if constexpr (std::is_void<CT>::value)
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(chi), "the tile fits the staging");
@@ -605,6 +610,17 @@ constexpr int hop_shape(int prec) {
 
 template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO>
 static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
+    if constexpr (DAG && !HASY && !NORM && !HALO) {
+        if (a.cg == CG_PRE) {
+            if constexpr (hop_shape(P) == 8) {
+                if (a.rows) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
+                else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
+            } else {
+                hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_PRE><<<grid, 256, a.lds_extra, st>>>(a);
+            }
+            return;
+        }
+    }
     if constexpr (hop_shape(P) == 1) {
         hop1_kernel<P, LK, DAG, HASY, NORM, NTM, HALO><<<grid, 64, 0, st>>>(a);
     } else if constexpr (hop_shape(P) == 8) {
@@ -728,7 +744,7 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     // 16^4 and smaller); from 24^4 up the single-wave rebuild is 0.5-2.5
     // points faster
     a.rows = LQCD_HOP_ROWS && a.g.vh < ((int64_t)1 << 17) && a.y[0] == nullptr &&
-             a.y[1] == nullptr && a.partial == nullptr && a.cg_x == nullptr;
+             a.y[1] == nullptr && a.partial == nullptr && a.cg != CG_UPDATE;
     const int64_t spinors = (int64_t)(nparity * half_spinor_bytes(a.g, prec));
     const int64_t links = (int64_t)gauge_bytes(a.g, prec, link);
     const bool out_nt = OUT_NT;
@@ -760,8 +776,11 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     }
     a.nblk = grid.x;
     const bool hasy = a.y[0] != nullptr || a.y[1] != nullptr;
-    const int norm = a.cg_x != nullptr ? 2 : a.partial != nullptr ? 1 : 0;
-    if (norm == 2 && (!hasy || !dag || !a.partial || !a.cg_p || !a.cg_alpha)) return LQCD_EINVAL;
+    const int norm = a.cg == CG_UPDATE ? 2 : a.partial != nullptr ? 1 : 0;
+    if (a.cg != CG_NONE && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
+    if (a.cg == CG_UPDATE && (!hasy || !a.partial)) return LQCD_EINVAL;
+    // a pre-summing launch has a block for every group
+    if (a.cg == CG_PRE && (hasy || norm || !a.groups || (int64_t)a.n_groups > a.bpp)) return LQCD_EINVAL;
     if (prec == LQCD_F64) {
         if (link == 18) launch_l<LQCD_F64, 18>(a, dag, hasy, norm, grid, st);
         else launch_l<LQCD_F64, 12>(a, dag, hasy, norm, grid, st);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "lqcd_internal.h"
+#include "reduce.h"
 
 namespace lqcd {
 
@@ -120,6 +121,32 @@ __host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t
     return (t * (uint32_t)g.st + (uint32_t)(j * g.st >> 3) + (TILE - 1)) >> TILE_SHIFT;
 }
 
+// Launches of the solver.  CG_UPDATE: the adjoint hop that completes A p and
+// does not store it: the epilogue does r -= alpha A p on out = r and leaves
+// the block partial of |r|^2.  alpha = rr / <p, A p> is formed by every block
+// on its own, from the <p, A p> partials where they are few, or from at most
+// CG_GROUPS sums which the hop launch before it (CG_PRE) makes of them on the
+// side, one run of them per block of its first blocks: no launch in between,
+// and every sum in a fixed order.
+enum { CG_NONE = 0, CG_PRE, CG_UPDATE };
+constexpr int CG_GROUPS = 128;
+// the solver's device scalars: the residual |r|^2 of the even and of the odd
+// iterations (an iteration reads the one before's), alpha, beta, and a value
+// for the host
+enum { CG_RR = 0, CG_ALPHA = 2, CG_BETA, CG_OUT, CG_SCALARS = 16 };
+
+// Sum of n values by one wave in a fixed order, the same in every lane.
+__device__ __forceinline__ double wave_total(const double *v, int n) {
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int i = (int)(threadIdx.x & 63);
+    for (; i + 192 < n; i += 256) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] += v[i + 64 * j];
+    }
+    for (; i < n; i += 64) a[0] += v[i];
+    return wave_sum((a[0] + a[1]) + (a[2] + a[3]));
+}
+
 // Cache-blocked tile order: tiles per z-group, z-groups per brick, Lt and
 // z-groups in Lz.  The plain order is the same formula with pt = bz = lz = 1
 // and lt larger than any tile index, so the traversal needs no branch on the
@@ -159,13 +186,13 @@ struct HopArgs {
     // face[0] (projected half-spinors of the forward neighbours) and face[1]
     // (U^dag times the projected backward neighbours) instead of `in`
     const char *face[2];
-    // CG-update launches (cg_x set): the result A p is not stored; the
-    // epilogue does x += alpha p, r -= alpha A p on out = r and writes the
-    // block partial of |r|^2, alpha read from the device (read late: the
-    // sixth line of the arguments)
-    char *cg_x;
-    const char *cg_p;
-    const double *cg_alpha;
+    // the solver's launches (read late: the sixth line of the arguments)
+    double *sc;           // its scalars
+    const double *sums;   // block sums to finish: CG_PRE all of them, CG_UPDATE the groups'
+    double *groups;       // CG_PRE: sums of n_groups runs of them
+    int n_sums, n_groups;
+    int cg;               // role of the launch
+    int slot;             // parity of the iteration (CG_RR)
     // host side: dynamic LDS bytes added to each 4-way block (limits the
     // blocks in flight per CU; not read by the kernels)
     uint32_t lds_extra;
