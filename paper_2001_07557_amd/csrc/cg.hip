@@ -102,8 +102,8 @@ constexpr int CG_MANY = 16384;
 constexpr int CG_FEW = 1024;
 template <int P>
 __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char *rs, char *xs, double *sc,
-                                                            const double *partial, int n, int stride,
-                                                            int slot, int64_t vh) {
+                                                            const double *partial, int n, int slot,
+                                                            int64_t vh) {
     using T = typename real_of<P>::type;
     const int64_t step = (int64_t)gridDim.x * SUM_BLOCK;
     int64_t s = (int64_t)blockIdx.x * SUM_BLOCK + threadIdx.x;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char 
     }
     const double old = sc[CG_RR + (slot ^ 1)];
     const T alpha = (T)sc[CG_ALPHA];
-    const double rr = partial_total(partial, n, stride);
+    const double rr = partial_total(partial, n, 1);
     const double b = old > 0.0 ? rr / old : 0.0;
     const T beta = (T)b;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -140,8 +140,10 @@ __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char 
     }
 }
 
-// x64 += xs + alpha p (inner precision; the step of the last iteration is
-// still pending), xs = 0.
+// x64 += xs + alpha p (the step of the last iteration is still pending; the
+// sum is rounded to the inner precision's storage like every step before it,
+// whose loss the residual then holds along p, the direction that is kept),
+// xs = 0.
 template <int P>
 __global__ __launch_bounds__(CG_BLOCK) void cg_fold_k(char *x64, char *xs, const char *p, const double *sc,
                                                       int64_t vh) {
@@ -155,35 +157,39 @@ __global__ __launch_bounds__(CG_BLOCK) void cg_fold_k(char *x64, char *xs, const
     load_spinor<P>(xs, s, v);
     load_spinor<P>(p, s, vp);
 #pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = {fmad(alpha, vp[k].re, v[k].re), fmad(alpha, vp[k].im, v[k].im)};
+    round_stored<P>(v);
+#pragma unroll
     for (int k = 0; k < 12; ++k) {
-        vx[k] = {vx[k].re + (double)fmad(alpha, vp[k].re, v[k].re),
-                 vx[k].im + (double)fmad(alpha, vp[k].im, v[k].im)};
+        vx[k] = {vx[k].re + (double)v[k].re, vx[k].im + (double)v[k].im};
         v[k] = {0, 0};
     }
     store_spinor<LQCD_F64>(x64, s, vx);
     store_spinor<P>(xs, s, v);
 }
 
-// r = b - r (FP64, in place), per-block |r|^2.
-__global__ __launch_bounds__(CG_BLOCK) void cg_residual_k(char *r, const char *b, int64_t vh,
-                                                          double *partial) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double acc[1] = {0.0};
+// Inner start from a zero guess: rs = b rounded to the inner precision, with
+// one |rs as stored|^2 partial per tile, and xs = p = 0.
+template <int P>
+__global__ __launch_bounds__(CG_BLOCK) void cg_start_k(char *rs, char *xs, char *p, const char *b,
+                                                       double *partial, int64_t vh) {
+    using T = typename real_of<P>::type;
+    const int64_t s = (int64_t)blockIdx.x * CG_BLOCK + threadIdx.x;
+    double n = 0.0;
     if (s < vh) {
-        cplx<double> vr[12], vb[12];
-        load_spinor<LQCD_F64>(r, s, vr);
+        cplx<double> vb[12];
+        cplx<T> v[12];
         load_spinor<LQCD_F64>(b, s, vb);
-        double nr = 0;
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            vr[k] = vb[k] - vr[k];
-            nr += norm2(vr[k]);
-        }
-        store_spinor<LQCD_F64>(r, s, vr);
-        acc[0] = nr;
+        for (int k = 0; k < 12; ++k) v[k] = {(T)vb[k].re, (T)vb[k].im};
+        n = (double)store_spinor<P>(rs, s, v, true);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = {0, 0};
+        store_spinor<P>(xs, s, v);
+        store_spinor<P>(p, s, v);
     }
-    block_sum<1>(acc);
-    if (threadIdx.x == 0) partial[blockIdx.x] = acc[0];
+    n = wave_sum(n);
+    if ((threadIdx.x & 63) == 0 && s < vh) partial[s >> TILE_SHIFT] = n;
 }
 
 // ---------------------------------------------------------------------------
@@ -192,22 +198,16 @@ __global__ __launch_bounds__(CG_BLOCK) void cg_residual_k(char *r, const char *b
 
 struct CGWork {
     char *xs, *rs, *p, *te, *to;      // inner precision
-    char *r64, *te64, *to64;          // FP64
-    double *partial;                  // of |r|^2 (and of the FP64 sums)
-    double *pap, *groups;             // of <p, A p>, in te64 (idle meanwhile)
+    char *te64, *to64;                // FP64
+    double *partial;                  // of |rs|^2, one per tile
+    // one per tile of <p, A p>, or of a recomputed |r|^2, or per block of an
+    // FP64 norm; and of runs of them
+    double *pap, *groups;
     double *sc;
     size_t bytes;
 };
 
 static size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
-
-static int64_t cg_partials(const Geom &g) {
-    const int64_t a = hop_partials(g, 1);
-    const int64_t b = (g.vh + CG_BLOCK - 1) / CG_BLOCK;
-    const int64_t c = reduce_blocks(g, 1) * 2;
-    int64_t m = a > b ? a : b;
-    return m > c ? m : c;
-}
 
 static CGWork cg_layout(const Geom &g, int prec, char *base) {
     CGWork w{};
@@ -224,14 +224,14 @@ static CGWork cg_layout(const Geom &g, int prec, char *base) {
     w.p = take(hb);
     w.te = take(hb);
     w.to = take(hb);
-    w.r64 = take(hb64);
+    // the sums' scratch has room to spare (1536 doubles per tile)
+    w.groups = (double *)take(hb64);
+    w.pap = base ? w.groups + CG_GROUPS : nullptr;
     w.te64 = take(hb64);
     w.to64 = take(hb64);
-    w.partial = (double *)take(sizeof(double) * cg_partials(g));
+    const int64_t tiles = hop_partials(g, 1), norms = 2 * reduce_blocks(g, 1);
+    w.partial = (double *)take(sizeof(double) * (tiles > norms ? tiles : norms));
     w.sc = (double *)take(sizeof(double) * CG_SCALARS);
-    // hop_partials(g, 1) + CG_GROUPS numbers, of the 1536 doubles per tile
-    w.groups = (double *)w.te64;
-    w.pap = base ? w.groups + CG_GROUPS : nullptr;
     w.bytes = off;
     return w;
 }
@@ -278,15 +278,15 @@ struct Solver {
     int link64;
     const char *U64;
     CGWork w;
-    int n_rr, stride_rr;  // the |rs|^2 partials in w.partial
-
     int hop(int out_par, char *out, const char *in, const char *y, double alpha, bool dag, int pr,
-            int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0) {
+            int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0, const char *rhs = nullptr) {
         HopArgs a{};
         a.cg = cg;
         a.slot = slot;
         a.sc = w.sc;
         a.groups = w.groups;
+        a.rhs = rhs;
+        a.stored = w.partial;
         const int n = (int)hop_partials(g, 1);
         const int per = (n + CG_GROUPS - 1) / CG_GROUPS;
         a.n_groups = (n + per - 1) / per;
@@ -312,7 +312,7 @@ struct Solver {
     int iterate(int slot) {
         const double k2 = -kappa * kappa;
         const double *sums = w.partial;
-        int n = n_rr, stride = stride_rr;
+        int n = (int)hop_partials(g, 1);
         if (n > CG_MANY) {
             cg_groups_k<<<CG_GROUPS, 64, 0, st>>>(w.partial, n, w.groups);
             sums = w.groups;
@@ -320,31 +320,17 @@ struct Solver {
         }
         const int64_t blocks = (g.vh + SUM_BLOCK - 1) / SUM_BLOCK;
         cg_direction_k<P><<<dim3((unsigned)(blocks < DIR_BLOCKS ? blocks : DIR_BLOCKS)), SUM_BLOCK, 0, st>>>(
-            w.p, w.rs, w.xs, w.sc, sums, n, stride, slot, g.vh);
+            w.p, w.rs, w.xs, w.sc, sums, n, slot, g.vh);
         int rc = check_launch();
         if (!rc) rc = hop(LQCD_ODD, w.to, w.p, nullptr, 1.0, false, P, link, U, nullptr);
         if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p, k2, false, P, link, U, w.pap);
         if (!rc) rc = hop(LQCD_ODD, w.to, w.te, nullptr, 1.0, true, P, link, U, nullptr,
                           hop_partials(g, 1) > CG_FEW ? CG_PRE : CG_NONE);
         if (!rc) rc = hop(LQCD_EVEN, w.rs, w.to, w.te, k2, true, P, link, U, w.partial, CG_UPDATE, slot);
-        n_rr = (int)hop_partials(g, 1);
-        stride_rr = 1;
-        return rc;
-    }
-
-    // out = Mhat^dag Mhat x; the block partials of |Mhat x|^2 go to `partial`
-    int apply_a(int pr, int lk, const char *U_, const char *x, char *out, char *te, char *to,
-                double *partial) {
-        const double k2 = -kappa * kappa;
-        int rc = hop(LQCD_ODD, to, x, nullptr, 1.0, false, pr, lk, U_, nullptr);
-        if (!rc) rc = hop(LQCD_EVEN, te, to, x, k2, false, pr, lk, U_, partial);
-        if (!rc) rc = hop(LQCD_ODD, to, te, nullptr, 1.0, true, pr, lk, U_, nullptr);
-        if (!rc) rc = hop(LQCD_EVEN, out, to, te, k2, true, pr, lk, U_, nullptr);
         return rc;
     }
 
     dim3 grid() const { return dim3((unsigned)((g.vh + CG_BLOCK - 1) / CG_BLOCK)); }
-    int64_t nblk() const { return (g.vh + CG_BLOCK - 1) / CG_BLOCK; }
 
     int read(double *host, int slot) {
         hipError_t e = hipMemcpyAsync(host, w.sc + slot, sizeof(double), hipMemcpyDeviceToHost, st);
@@ -356,30 +342,30 @@ struct Solver {
         return LQCD_OK;
     }
 
-    // the block partials of |v|^2 of an FP64 or inner-precision half field
-    int norm_partials(const char *v, int pr) {
-        launch_reduce(g, 1, v, nullptr, pr, w.partial, st);
-        n_rr = (int)reduce_blocks(g, 1);
-        stride_rr = 2;
-        return check_launch();
+    // |v|^2 of an FP64 half field on the host
+    int norm64(const char *v, double *host) {
+        launch_reduce(g, 1, v, nullptr, LQCD_F64, w.pap, st);
+        return total<false>(w.pap, (int)reduce_blocks(g, 1), 2, host);
     }
 
-    // their sum on the host
-    int total(double *host) {
-        cg_sum_k<false><<<1, SUM_BLOCK, 0, st>>>(w.partial, n_rr, stride_rr, w.sc);
+    // the sum of n partials on the host
+    template <bool RESID>
+    int total(const double *partial, int n, int stride, double *host) {
+        cg_sum_k<RESID><<<1, SUM_BLOCK, 0, st>>>(partial, n, stride, w.sc);
         const int rc = check_launch();
         return rc ? rc : read(host, CG_OUT);
     }
 
-    // r64 = b - A64 x64; returns |r64|^2 on the host
+    // The inner residual from the true one: rs = b - A64 x64 (FP64, rounded to
+    // the inner precision) with its partials, |b - A64 x64|^2 on the host.
+    template <int P>
     int true_residual(char *x64, const char *b, double *rr) {
-        int rc = apply_a(LQCD_F64, link64, U64, x64, w.r64, w.te64, w.to64, nullptr);
-        if (rc) return rc;
-        cg_residual_k<<<grid(), CG_BLOCK, 0, st>>>(w.r64, b, g.vh, w.partial);
-        cg_sum_k<true><<<1, SUM_BLOCK, 0, st>>>(w.partial, (int)nblk(), 1, w.sc);
-        rc = check_launch();
-        if (rc) return rc;
-        return read(rr, CG_OUT);
+        const double k2 = -kappa * kappa;
+        int rc = hop(LQCD_ODD, w.to64, x64, nullptr, 1.0, false, LQCD_F64, link64, U64, nullptr);
+        if (!rc) rc = hop(LQCD_EVEN, w.te64, w.to64, x64, k2, false, LQCD_F64, link64, U64, nullptr);
+        if (!rc) rc = hop(LQCD_ODD, w.to64, w.te64, nullptr, 1.0, true, LQCD_F64, link64, U64, nullptr);
+        if (!rc) rc = hop(LQCD_EVEN, w.rs, w.to64, w.te64, k2, true, LQCD_F64, link64, U64, w.pap, CG_RESID + P, 0, b);
+        return rc ? rc : total<true>(w.pap, (int)hop_partials(g, 1), 1, rr);
     }
 
     template <int P>
@@ -388,8 +374,7 @@ struct Solver {
         stats->iterations = 0;
         stats->reliable_updates = 0;
         double bb = 0.0;
-        int rc = norm_partials(b, LQCD_F64);
-        if (!rc) rc = total(&bb);
+        int rc = norm64(b, &bb);
         if (rc) return rc;
         if (!std::isfinite(bb)) return LQCD_ENAN;
         if (bb == 0.0) {
@@ -408,34 +393,31 @@ struct Solver {
         // a zero starting guess (the common case) needs no FP64 operator
         // application: r = b
         double xx = 0.0;
-        rc = norm_partials(x64, LQCD_F64);
-        if (!rc) rc = total(&xx);
+        rc = norm64(x64, &xx);
         if (rc) return rc;
-        if (xx == 0.0) {
-            launch_convert(g, 1, w.r64, LQCD_F64, b, LQCD_F64, st);
-            rc = check_launch();
-            rr = bb;
-        } else {
-            rc = true_residual(x64, b, &rr);
-        }
+        if (xx == 0.0) rr = bb;
+        else rc = true_residual<P>(x64, b, &rr);
         if (rc) return rc;
         if (!std::isfinite(rr)) return LQCD_ENAN;
         stats->true_residual = std::sqrt(rr / bb);
         stats->iterated_residual = stats->true_residual;
         if (rr <= target) return LQCD_OK;
 
-        // inner start: rs = r64, xs = 0, and p = 0 with beta = alpha = 0 for
-        // the first direction update
-        const size_t hb = half_spinor_bytes(g, P);
-        hipError_t e = hipMemsetAsync(w.xs, 0, hb, st);
-        if (e == hipSuccess) e = hipMemsetAsync(w.p, 0, hb, st);
-        if (e == hipSuccess) e = hipMemsetAsync(w.sc, 0, sizeof(double) * CG_SCALARS, st);
+        // inner start: rs = b - A x, xs = 0, and p = 0 with beta = alpha = 0
+        // for the first direction update
+        hipError_t e = hipMemsetAsync(w.sc, 0, sizeof(double) * CG_SCALARS, st);
+        if (xx == 0.0) {
+            cg_start_k<P><<<grid(), CG_BLOCK, 0, st>>>(w.rs, w.xs, w.p, b, w.partial, g.vh);
+            rc = check_launch();
+        } else {
+            const size_t hb = half_spinor_bytes(g, P);
+            if (e == hipSuccess) e = hipMemsetAsync(w.xs, 0, hb, st);
+            if (e == hipSuccess) e = hipMemsetAsync(w.p, 0, hb, st);
+        }
         if (e != hipSuccess) {
             set_hip_error(e);
             return LQCD_EHIP;
         }
-        launch_convert(g, 1, w.rs, P, w.r64, LQCD_F64, st);
-        rc = norm_partials(w.rs, P);
         if (rc) return rc;
 
         int k = 0;
@@ -458,7 +440,7 @@ struct Solver {
             ++k;
             bool reliable = reliable_every > 0 && k % reliable_every == 0;
             if (reliable || k >= next_read || k >= maxiter) {
-                rc = total(&rr_it);
+                rc = total<false>(w.partial, (int)hop_partials(g, 1), 1, &rr_it);
                 if (rc) return rc;
                 if (!std::isfinite(rr_it)) {
                     stats->iterations = k;
@@ -476,7 +458,7 @@ struct Solver {
             }
             if (reliable || k >= maxiter) {
                 cg_fold_k<P><<<grid(), CG_BLOCK, 0, st>>>(x64, w.xs, w.p, w.sc, g.vh);
-                rc = true_residual(x64, b, &rr);
+                rc = true_residual<P>(x64, b, &rr);
                 if (rc) return rc;
                 stats->reliable_updates += 1;
                 stats->iterations = k;
@@ -486,10 +468,7 @@ struct Solver {
                 if (rr <= target) return LQCD_OK;
                 if (k >= maxiter) return LQCD_ENOCONV;
                 rr_ref = rr;
-                // restart the inner residual from the FP64 one, keep p
-                launch_convert(g, 1, w.rs, P, w.r64, LQCD_F64, st);
-                rc = norm_partials(w.rs, P);
-                if (rc) return rc;
+                // the inner residual restarts from the FP64 one, p is kept
                 rr_seen = rr;
                 k_seen = k;
                 next_read = k + read_gap(iterations_left(rr, rate, target_inner));

@@ -161,6 +161,27 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t 
     return nrm;
 }
 
+// CG_RESID: r = rhs - (alpha acc + y) of the site, stored in precision PI;
+// nrm = |r|^2 in FP64 and |r as stored|^2.
+template <int P, int PI>
+__device__ __forceinline__ void cg_residual(const HopArgs &a, int p, int64_t s,
+                                            cplx<typename real_of<P>::type> acc[12], double nrm[2]) {
+    using TI = typename real_of<PI>::type;
+    hop_combine<P, true>(a, p, s, acc);
+    cplx<double> b[12];
+    cplx<TI> r[12];
+    load_spinor<LQCD_F64>(a.rhs, s, b);
+    double n = 0.0;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        b[k] = {b[k].re - acc[k].re, b[k].im - acc[k].im};
+        n += norm2(b[k]);
+        r[k] = {(TI)b[k].re, (TI)b[k].im};
+    }
+    nrm[0] = n;
+    nrm[1] = (double)store_spinor<PI>(a.out[p], s, r, true);
+}
+
 // CG_UPDATE: alpha of this iteration, formed by one wave; block 0 keeps it.
 __device__ __forceinline__ double cg_alpha_of(const HopArgs &a) {
     const double pap = wave_total(a.sums, a.n_sums);
@@ -281,13 +302,15 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     }
     if (CG == CG_PRE && w == 3) cg_presum(a);
     __syncthreads();
-    double nrm[1] = {0.0};
+    double nrm[2] = {0.0, 0.0};
     if (w == 0 && active) {
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[j][k][lane];
-        if constexpr (std::is_void<CT>::value)
+        if constexpr (CG >= CG_RESID)
+            cg_residual<P, CG - CG_RESID>(a, p, s, acc, nrm);
+        else if constexpr (std::is_void<CT>::value)
             nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
@@ -300,6 +323,10 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         if (w == 0) {
             const double t = wave_sum(nrm[0]);
             if (lane == 0 && blk < a.g.ntiles) a.partial[blk] = t;
+            if constexpr (CG >= CG_RESID) {
+                const double u = wave_sum(nrm[1]);
+                if (lane == 0 && blk < a.g.ntiles) a.stored[blk] = u;
+            }
         }
     }
 }
@@ -610,6 +637,19 @@ constexpr int hop_shape(int prec) {
 
 template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO>
 static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
+    if constexpr (P == LQCD_F64 && DAG && HASY && NORM == 1 && !HALO) {
+        if (a.cg >= CG_RESID) {
+#define LQCD_RESID(PI)                                                                             \
+    if (a.cg == CG_RESID + PI) {                                                                   \
+        hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI><<<grid, 256, a.lds_extra, st>>>(a); \
+        return;                                                                                    \
+    }
+            LQCD_RESID(LQCD_F64)
+            LQCD_RESID(LQCD_F32)
+            LQCD_RESID(LQCD_F16)
+#undef LQCD_RESID
+        }
+    }
     if constexpr (DAG && !HASY && !NORM && !HALO) {
         if (a.cg == CG_PRE) {
             if constexpr (hop_shape(P) == 8) {
@@ -777,7 +817,9 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     a.nblk = grid.x;
     const bool hasy = a.y[0] != nullptr || a.y[1] != nullptr;
     const int norm = a.cg == CG_UPDATE ? 2 : a.partial != nullptr ? 1 : 0;
-    if (a.cg != CG_NONE && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
+    if (a.cg != CG_NONE && a.cg < CG_RESID && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
+    if (a.cg >= CG_RESID && (prec != LQCD_F64 || !dag || !hasy || norm != 1 || !a.rhs || !a.stored))
+        return LQCD_EINVAL;
     if (a.cg == CG_UPDATE && (!hasy || !a.partial)) return LQCD_EINVAL;
     // a pre-summing launch has a block for every group
     if (a.cg == CG_PRE && (hasy || norm || !a.groups || (int64_t)a.n_groups > a.bpp)) return LQCD_EINVAL;

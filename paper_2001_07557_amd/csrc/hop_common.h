@@ -128,7 +128,11 @@ __host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t
 // CG_GROUPS sums which the hop launch before it (CG_PRE) makes of them on the
 // side, one run of them per block of its first blocks: no launch in between,
 // and every sum in a fixed order.
-enum { CG_NONE = 0, CG_PRE, CG_UPDATE };
+// CG_RESID + P: the FP64 adjoint hop that completes A x of a reliable update:
+// the epilogue forms r = rhs - A x, leaves the block partials of |r|^2, rounds
+// r to the inner precision P, stores it as the inner residual and leaves the
+// partials of |r as stored|^2.
+enum { CG_NONE = 0, CG_PRE, CG_UPDATE, CG_RESID };
 constexpr int CG_GROUPS = 128;
 // the solver's device scalars: the residual |r|^2 of the even and of the odd
 // iterations (an iteration reads the one before's), alpha, beta, and a value
@@ -191,6 +195,9 @@ struct HopArgs {
     const double *sums;   // block sums to finish: CG_PRE all of them, CG_UPDATE the groups'
     double *groups;       // CG_PRE: sums of n_groups runs of them
     int n_sums, n_groups;
+    // CG_RESID: right-hand side, and the partials of |r|^2 as stored
+    const char *rhs;
+    double *stored;
     int cg;               // role of the launch
     int slot;             // parity of the iteration (CG_RR)
     // host side: dynamic LDS bytes added to each 4-way block (limits the

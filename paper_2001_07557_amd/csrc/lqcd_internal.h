@@ -311,9 +311,15 @@ __device__ __forceinline__ void put(V *p, V v) {
     else *p = v;
 }
 
+// `norm` (a constant): returns |stored values|^2 of the site, else 0.
 template <int P, bool NT = false>
-__device__ __forceinline__ void store_spinor(char *__restrict__ base, int64_t s,
-                                             const cplx<typename real_of<P>::type> v[12]) {
+__device__ __forceinline__ typename real_of<P>::type store_spinor(
+    char *__restrict__ base, int64_t s, const cplx<typename real_of<P>::type> v[12], bool norm = false) {
+    typename real_of<P>::type nr = 0;
+    if (norm && P != LQCD_F16) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) nr += norm2(v[k]);
+    }
     const int64_t tile = s >> TILE_SHIFT;
     const int lane = (int)(s & (TILE - 1));
     char *t = base + tile * spinor_tile_bytes(P);
@@ -348,10 +354,31 @@ __device__ __forceinline__ void store_spinor(char *__restrict__ base, int64_t s,
             for (int j = 0; j < 4; ++j) {
                 __half2 h = __floats2half2_rn(v[4 * k + j].re * inv, v[4 * k + j].im * inv);
                 u[j] = *reinterpret_cast<uint32_t *>(&h);
+                if (norm) {
+                    const float2 f = __half22float2(h);
+                    nr += norm2(cplx<float>{f.x * m, f.y * m});
+                }
             }
             put<NT>(&w[k * TILE], v4u{u[0], u[1], u[2], u[3]});
         }
         put<NT>(reinterpret_cast<float *>(t + 3 * TILE * WORD) + lane, m);
+    }
+    return nr;
+}
+
+// v as store_spinor would store it.
+template <int P>
+__device__ __forceinline__ void round_stored(cplx<typename real_of<P>::type> v[12]) {
+    if constexpr (P == LQCD_F16) {
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
+        const float inv = 1.f / (m > 0.f ? m : 1.f);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const float2 f = __half22float2(__floats2half2_rn(v[k].re * inv, v[k].im * inv));
+            v[k] = {f.x * m, f.y * m};
+        }
     }
 }
 
