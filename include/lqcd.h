@@ -294,7 +294,9 @@ size_t lqcd_cg_workspace_bytes(const lqcd_geom_t *g, int inner_prec, int inner_l
  *   The inner loop runs CG in inner_prec with FP64 block and grid sums.
  *   A reliable update folds the inner solution into x_e, recomputes the true
  *   residual in FP64 and restarts the inner residual from it, keeping the
- *   search direction; it is taken every `reliable_every` iterations (0 =
+ *   search direction unless the recomputed |r|^2 exceeds the inner one by a
+ *   fifth (the recurrence has drifted: the direction restarts from the
+ *   residual as well); it is taken every `reliable_every` iterations (0 =
  *   never on a schedule), whenever the inner residual has fallen since the
  *   last update by 1000x (FP32 inner) or 10x (F16 inner), beyond which the
  *   inner recurrence is not trusted (for FP32 inner iterations put off, by

@@ -92,7 +92,8 @@ __global__ __launch_bounds__(64) void cg_groups_k(const double *partial, int n, 
 
 // x += alpha p, p = rs + beta p.  Every block sums the n partials of |rs|^2
 // (few blocks, each over several sites per thread) and forms beta = |rs|^2 /
-// |rs before|^2; the first iteration finds 0 there and takes p = rs.
+// |rs before|^2; the first iteration finds 0 there and takes p = rs, and so
+// does a restart.
 constexpr int DIR_BLOCKS = 512;
 // partials beyond which they are summed into groups by a launch of their own
 constexpr int CG_MANY = 16384;
@@ -103,7 +104,7 @@ constexpr int CG_FEW = 1024;
 template <int P>
 __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char *rs, char *xs, double *sc,
                                                             const double *partial, int n, int slot,
-                                                            int64_t vh) {
+                                                            bool restart, int64_t vh) {
     using T = typename real_of<P>::type;
     const int64_t step = (int64_t)gridDim.x * SUM_BLOCK;
     int64_t s = (int64_t)blockIdx.x * SUM_BLOCK + threadIdx.x;
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char 
     const double old = sc[CG_RR + (slot ^ 1)];
     const T alpha = (T)sc[CG_ALPHA];
     const double rr = partial_total(partial, n, 1);
-    const double b = old > 0.0 ? rr / old : 0.0;
+    const double b = old > 0.0 && !restart ? rr / old : 0.0;
     const T beta = (T)b;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc[CG_RR + slot] = rr;
@@ -268,6 +269,17 @@ static int read_gap(int left) {
 // iterations instead of 46).
 constexpr int DRIFT_DEFER = CHECK_EVERY;
 constexpr double DRIFT_HARD = 1e-4;
+// A reliable update keeps p while the recomputed residual agrees with the
+// recurrence's, and restarts from p = r where it is RESTART times larger
+// (squared norms): between two host reads a binary16 recurrence can fall a
+// thousand times below the true residual, beta = |r true|^2 / |r before|^2
+// then weighs the old p a hundredfold, and the solve crawls.  Measured
+// (iterations / updates to 1e-10, binary16 inner, p always kept -> 1.2): Haar
+// links 8^4 761/9 -> 29/4; links spread by 0.4 around one 16^4 63/7 -> 37/5;
+// by 0.3 24^3x48 50/6 -> 46/5 (7.41 -> 6.60 ms), 32^4 50/6 -> 46/5 (10.6 ->
+// 9.5 ms); by 0.2 75/8 either way.  1.02 restarts too often (48 to 50
+// iterations by 0.3), 1.5 and 2 miss the cases by 0.3, 16 those by 0.4.
+constexpr double RESTART = 1.2;
 
 struct Solver {
     Geom g;
@@ -309,7 +321,7 @@ struct Solver {
     // then Mhat^dag te = A p formed inside the last hop, which updates rs and
     // leaves its |rs|^2 partials.
     template <int P>
-    int iterate(int slot) {
+    int iterate(int slot, bool restart) {
         const double k2 = -kappa * kappa;
         const double *sums = w.partial;
         int n = (int)hop_partials(g, 1);
@@ -320,7 +332,7 @@ struct Solver {
         }
         const int64_t blocks = (g.vh + SUM_BLOCK - 1) / SUM_BLOCK;
         cg_direction_k<P><<<dim3((unsigned)(blocks < DIR_BLOCKS ? blocks : DIR_BLOCKS)), SUM_BLOCK, 0, st>>>(
-            w.p, w.rs, w.xs, w.sc, sums, n, slot, g.vh);
+            w.p, w.rs, w.xs, w.sc, sums, n, slot, restart, g.vh);
         int rc = check_launch();
         if (!rc) rc = hop(LQCD_ODD, w.to, w.p, nullptr, 1.0, false, P, link, U, nullptr);
         if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p, k2, false, P, link, U, w.pap);
@@ -421,6 +433,7 @@ struct Solver {
         if (rc) return rc;
 
         int k = 0;
+        bool restart = false;
         double rr_it = rr;
         double rr_ref = rr;  // true residual at the last reliable update
         const double delta = P == LQCD_F64 ? 0.0 : P == LQCD_F32 ? DELTA_F32 : DELTA_F16;
@@ -435,7 +448,8 @@ struct Solver {
         double rate = 0.0;
         int next_read = CHECK_EVERY;
         while (true) {
-            rc = iterate<P>(k & 1);
+            rc = iterate<P>(k & 1, restart);
+            restart = false;
             if (rc) return rc;
             ++k;
             bool reliable = reliable_every > 0 && k % reliable_every == 0;
@@ -468,7 +482,8 @@ struct Solver {
                 if (rr <= target) return LQCD_OK;
                 if (k >= maxiter) return LQCD_ENOCONV;
                 rr_ref = rr;
-                // the inner residual restarts from the FP64 one, p is kept
+                // the inner residual restarts from the FP64 one
+                restart = rr > RESTART * rr_it;
                 rr_seen = rr;
                 k_seen = k;
                 next_read = k + read_gap(iterations_left(rr, rate, target_inner));
