@@ -10,11 +10,15 @@
 // iterations, and every iteration once the decay so far says the tolerance
 // is near, so the solve stops at the first iteration that reaches it.
 //
-// Per iteration five launches: the direction update (x += a p, p = r + b p;
+// Per iteration five launches (four, below, on small lattices): the direction update (x += a p, p = r + b p;
 // its blocks finish the |r|^2 sum and form beta themselves), four hops (the
 // second leaves the |Mhat p|^2 = <p, A p> block partials, the third sums runs
 // of them on the side, the fourth forms alpha from those, does r -= a A p in
 // its epilogue, so A p is never stored, and leaves the |r|^2 partials).
+// On small lattices (CG_FEW partials, FP64 and FP32 inner) the direction
+// update is part of the first two hops and an iteration is four launches:
+// 16^4 FP32 5.4 + 6.3 + 5.7 + 6.5 + 5.8 -> 7.7 + 7.2 + 5.4 + 6.7 us under the
+// trace and one gap less, 4.53 -> 4.21 ms for a differentiable solve.
 // Kernel times per iteration (us, trace; seven launches before, with two
 // one-block scalar kernels and x updated in the fourth hop): 32^4 binary16
 // inner 26 + 30 + 26 + 43 + 12.5 + 2 x 4.9 -> 26 + 30 + 26 + 35 + 23, 24^3x48
@@ -23,6 +27,7 @@
 
 #include <chrono>
 #include <cmath>
+#include <utility>
 
 #include "lqcd_internal.h"
 #include "reduce.h"
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(64) void cg_groups_k(const double *partial, int n, 
     if (threadIdx.x == 0) groups[blockIdx.x] = t;
 }
 
-// x += alpha p, p = rs + beta p.  Every block sums the n partials of |rs|^2
+// x += alpha p, p_new = rs + beta p.  Every block sums the n partials of |rs|^2
 // (few blocks, each over several sites per thread) and forms beta = |rs|^2 /
 // |rs before|^2; the first iteration finds 0 there and takes p = rs, and so
 // does a restart.
@@ -102,7 +107,8 @@ constexpr int CG_MANY = 16384;
 // of its blocks run at once, put 0.9 us on a 5.2 us launch
 constexpr int CG_FEW = 1024;
 template <int P>
-__global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char *rs, char *xs, double *sc,
+__global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p_new, const char *p, const char *rs,
+                                                            char *xs, double *sc,
                                                             const double *partial, int n, int slot,
                                                             bool restart, int64_t vh) {
     using T = typename real_of<P>::type;
@@ -131,7 +137,7 @@ __global__ __launch_bounds__(SUM_BLOCK) void cg_direction_k(char *p, const char 
             vp[k] = {fmad(beta, vp[k].re, vr[k].re), fmad(beta, vp[k].im, vr[k].im)};
         }
         store_spinor<P>(xs, s, vx);
-        store_spinor<P>(p, s, vp);
+        store_spinor<P>(p_new, s, vp);
         s += step;
         if (s < vh) {
             load_spinor<P>(rs, s, vr);
@@ -198,8 +204,9 @@ __global__ __launch_bounds__(CG_BLOCK) void cg_start_k(char *rs, char *xs, char 
 // ---------------------------------------------------------------------------
 
 struct CGWork {
-    char *xs, *rs, *p, *te, *to;      // inner precision
-    char *te64, *to64;                // FP64
+    char *xs, *rs, *te, *to;          // inner precision
+    char *p[2];                       // this and the next direction
+    char *te64, *to64;                // FP64 (those of an FP64 inner solve)
     double *partial;                  // of |rs|^2, one per tile
     // one per tile of <p, A p>, or of a recomputed |r|^2, or per block of an
     // FP64 norm; and of runs of them
@@ -222,17 +229,26 @@ static CGWork cg_layout(const Geom &g, int prec, char *base) {
     };
     w.xs = take(hb);
     w.rs = take(hb);
-    w.p = take(hb);
+    w.p[0] = take(hb);
     w.te = take(hb);
     w.to = take(hb);
-    // the sums' scratch has room to spare (1536 doubles per tile)
-    w.groups = (double *)take(hb64);
-    w.pap = base ? w.groups + CG_GROUPS : nullptr;
-    w.te64 = take(hb64);
-    w.to64 = take(hb64);
+    // one FP64 field for the sums and, behind them, the second direction of a
+    // reduced inner precision; an FP64 inner solve has the second direction in
+    // the FP64 temporaries' place, which are its own
+    char *scratch = take(hb64);
+    char *t64[2] = {take(hb64), take(hb64)};
     const int64_t tiles = hop_partials(g, 1), norms = 2 * reduce_blocks(g, 1);
     w.partial = (double *)take(sizeof(double) * (tiles > norms ? tiles : norms));
     w.sc = (double *)take(sizeof(double) * CG_SCALARS);
+    if (base) {
+        w.groups = (double *)scratch;
+        w.pap = w.groups + CG_GROUPS;
+        // (sums: at most 128 + V/64 doubles of the 1536 per tile)
+        w.p[1] = prec == LQCD_F64 ? t64[0]
+                                  : scratch + align256(sizeof(double) * (CG_GROUPS + (tiles > norms ? tiles : norms)));
+        w.te64 = prec == LQCD_F64 ? w.te : t64[0];
+        w.to64 = prec == LQCD_F64 ? w.to : t64[1];
+    }
     w.bytes = off;
     return w;
 }
@@ -291,7 +307,8 @@ struct Solver {
     const char *U64;
     CGWork w;
     int hop(int out_par, char *out, const char *in, const char *y, double alpha, bool dag, int pr,
-            int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0, const char *rhs = nullptr) {
+            int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0, const char *rhs = nullptr,
+            bool restart = false) {
         HopArgs a{};
         a.cg = cg;
         a.slot = slot;
@@ -304,6 +321,11 @@ struct Solver {
         a.n_groups = (n + per - 1) / per;
         a.sums = cg == CG_PRE || n <= CG_FEW ? w.pap : w.groups;
         a.n_sums = cg == CG_PRE || n <= CG_FEW ? n : a.n_groups;
+        if (cg == CG_DIR_IN) a.sums = w.partial;  // n <= CG_FEW
+        a.restart = restart ? 1 : 0;
+        a.p_old = w.p[0];
+        a.p_new = w.p[1];
+        a.x = w.xs;
         a.g = g;
         a.U = U_;
         a.alpha = alpha;
@@ -317,27 +339,35 @@ struct Solver {
     }
 
     // One inner iteration: the direction update from the |rs|^2 partials of
-    // the step before, te = Mhat p with the <p, A p> = |Mhat p|^2 partials,
-    // then Mhat^dag te = A p formed inside the last hop, which updates rs and
-    // leaves its |rs|^2 partials.
+    // the step before (a launch of its own, or inside the first two hops),
+    // te = Mhat p with the <p, A p> = |Mhat p|^2 partials, then Mhat^dag te =
+    // A p formed inside the last hop, which updates rs and leaves its |rs|^2
+    // partials.
     template <int P>
     int iterate(int slot, bool restart) {
         const double k2 = -kappa * kappa;
-        const double *sums = w.partial;
-        int n = (int)hop_partials(g, 1);
-        if (n > CG_MANY) {
-            cg_groups_k<<<CG_GROUPS, 64, 0, st>>>(w.partial, n, w.groups);
-            sums = w.groups;
-            n = CG_GROUPS;
+        int n = (int)hop_partials(g, 1), rc = LQCD_OK;
+        const bool few = n <= CG_FEW;
+        if (P != LQCD_F16 && few) {
+            rc = hop(LQCD_ODD, w.to, w.rs, nullptr, 1.0, false, P, link, U, nullptr, CG_DIR_IN, slot, nullptr, restart);
+            if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.rs, k2, false, P, link, U, w.pap, CG_DIR_Y);
+            std::swap(w.p[0], w.p[1]);
+        } else {
+            const double *sums = w.partial;
+            if (n > CG_MANY) {
+                cg_groups_k<<<CG_GROUPS, 64, 0, st>>>(w.partial, n, w.groups);
+                sums = w.groups;
+                n = CG_GROUPS;
+            }
+            const int64_t blocks = (g.vh + SUM_BLOCK - 1) / SUM_BLOCK;
+            cg_direction_k<P><<<dim3((unsigned)(blocks < DIR_BLOCKS ? blocks : DIR_BLOCKS)), SUM_BLOCK, 0, st>>>(
+                w.p[1], w.p[0], w.rs, w.xs, w.sc, sums, n, slot, restart, g.vh);
+            std::swap(w.p[0], w.p[1]);
+            rc = check_launch();
+            if (!rc) rc = hop(LQCD_ODD, w.to, w.p[0], nullptr, 1.0, false, P, link, U, nullptr);
+            if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p[0], k2, false, P, link, U, w.pap);
         }
-        const int64_t blocks = (g.vh + SUM_BLOCK - 1) / SUM_BLOCK;
-        cg_direction_k<P><<<dim3((unsigned)(blocks < DIR_BLOCKS ? blocks : DIR_BLOCKS)), SUM_BLOCK, 0, st>>>(
-            w.p, w.rs, w.xs, w.sc, sums, n, slot, restart, g.vh);
-        int rc = check_launch();
-        if (!rc) rc = hop(LQCD_ODD, w.to, w.p, nullptr, 1.0, false, P, link, U, nullptr);
-        if (!rc) rc = hop(LQCD_EVEN, w.te, w.to, w.p, k2, false, P, link, U, w.pap);
-        if (!rc) rc = hop(LQCD_ODD, w.to, w.te, nullptr, 1.0, true, P, link, U, nullptr,
-                          hop_partials(g, 1) > CG_FEW ? CG_PRE : CG_NONE);
+        if (!rc) rc = hop(LQCD_ODD, w.to, w.te, nullptr, 1.0, true, P, link, U, nullptr, few ? CG_NONE : CG_PRE);
         if (!rc) rc = hop(LQCD_EVEN, w.rs, w.to, w.te, k2, true, P, link, U, w.partial, CG_UPDATE, slot);
         return rc;
     }
@@ -419,12 +449,12 @@ struct Solver {
         // for the first direction update
         hipError_t e = hipMemsetAsync(w.sc, 0, sizeof(double) * CG_SCALARS, st);
         if (xx == 0.0) {
-            cg_start_k<P><<<grid(), CG_BLOCK, 0, st>>>(w.rs, w.xs, w.p, b, w.partial, g.vh);
+            cg_start_k<P><<<grid(), CG_BLOCK, 0, st>>>(w.rs, w.xs, w.p[0], b, w.partial, g.vh);
             rc = check_launch();
         } else {
             const size_t hb = half_spinor_bytes(g, P);
             if (e == hipSuccess) e = hipMemsetAsync(w.xs, 0, hb, st);
-            if (e == hipSuccess) e = hipMemsetAsync(w.p, 0, hb, st);
+            if (e == hipSuccess) e = hipMemsetAsync(w.p[0], 0, hb, st);
         }
         if (e != hipSuccess) {
             set_hip_error(e);
@@ -471,7 +501,7 @@ struct Solver {
                 k_seen = k;
             }
             if (reliable || k >= maxiter) {
-                cg_fold_k<P><<<grid(), CG_BLOCK, 0, st>>>(x64, w.xs, w.p, w.sc, g.vh);
+                cg_fold_k<P><<<grid(), CG_BLOCK, 0, st>>>(x64, w.xs, w.p[0], w.sc, g.vh);
                 rc = true_residual<P>(x64, b, &rr);
                 if (rc) return rc;
                 stats->reliable_updates += 1;

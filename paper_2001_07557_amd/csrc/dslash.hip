@@ -105,16 +105,21 @@ constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #endif
 constexpr int64_t INFINITY_CACHE_BYTES = (int64_t)256 << 20;
 
-// acc = alpha acc + beta y.  The fused product is spelled out, so that every
+// acc = alpha acc + beta y (DIR: y is the new direction).  The fused product is spelled out, so that every
 // instance rounds alike (the compiler may fuse either one).
-template <int P, bool HASY>
+template <int P>
+__device__ __forceinline__ void cg_new_p(const HopArgs &a, int p, int64_t s,
+                                         cplx<typename real_of<P>::type> v[12]);
+
+template <int P, bool HASY, bool DIR = false>
 __device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
                                             cplx<typename real_of<P>::type> acc[12]) {
     using T = typename real_of<P>::type;
     const T alpha = (T)a.alpha;
     if constexpr (HASY) {
         cplx<T> y[12];
-        load_spinor<P>(a.y[p], s, y);
+        if constexpr (DIR) cg_new_p<P>(a, p, s, y);
+        else load_spinor<P>(a.y[p], s, y);
         const T beta = (T)a.beta;
 #pragma unroll
         for (int k = 0; k < 12; ++k)
@@ -131,12 +136,12 @@ __device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
 // returns |r|^2 of the site.  x += alpha p waits for the pass that reads p
 // next anyway (the direction update): one vector less per iteration, and
 // fewer registers here.
-template <int P, bool HASY, int NORM, bool NT>
+template <int P, bool HASY, int NORM, bool NT, bool DIR = false>
 __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t s,
                                                cplx<typename real_of<P>::type> acc[12],
                                                double cg_alpha = 0.0) {
     using T = typename real_of<P>::type;
-    hop_combine<P, HASY>(a, p, s, acc);
+    hop_combine<P, HASY, DIR>(a, p, s, acc);
     if constexpr (NORM == 2) {
         const T c = (T)cg_alpha;
         cplx<T> vr[12];
@@ -180,6 +185,31 @@ __device__ __forceinline__ void cg_residual(const HopArgs &a, int p, int64_t s,
     }
     nrm[0] = n;
     nrm[1] = (double)store_spinor<PI>(a.out[p], s, r, true);
+}
+
+// CG_DIR_Y, wave 1: x += alpha p old of the site; wave 2: the new p.  Both
+// wait for nothing that wave 0 does.
+template <int P>
+__device__ __forceinline__ void cg_step_x(const HopArgs &a, int64_t s) {
+    using T = typename real_of<P>::type;
+    const T c = (T)a.sc[CG_ALPHA];
+    cplx<T> vp[12], vx[12];
+    load_spinor<P>(a.p_old, s, vp);
+    load_spinor<P>(a.x, s, vx);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) vx[k] = {fmad(c, vp[k].re, vx[k].re), fmad(c, vp[k].im, vx[k].im)};
+    store_spinor<P>(a.x, s, vx);
+}
+template <int P>
+__device__ __forceinline__ void cg_new_p(const HopArgs &a, int p, int64_t s,
+                                         cplx<typename real_of<P>::type> v[12]) {
+    using T = typename real_of<P>::type;
+    const T b = (T)a.sc[CG_BETA];
+    cplx<T> vp[12];
+    load_spinor<P>(a.y[p], s, v);  // r
+    load_spinor<P>(a.p_old, s, vp);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = {fmad(b, vp[k].re, v[k].re), fmad(b, vp[k].im, v[k].im)};
 }
 
 // CG_UPDATE: alpha of this iteration, formed by one wave; block 0 keeps it.
@@ -277,18 +307,23 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     const int64_t s = hop_site_index(a, lane, p, blk);
     const Geom &g = a.g;
     const bool active = s < g.vh;
-    // (coordinates of a padding site are never used, and s < 2^31 anyway)
-    const Coord c = cb_coords(g, p, s);
+    // (coordinates of a padding site are never used, and s < 2^31 anyway;
+    // CG_DIR_IN sums with whole waves, whose lanes past the last site repeat
+    // its hops)
+    const int64_t sl = CG == CG_DIR_IN && !active ? g.vh - 1 : s;
+    const Coord c = cb_coords(g, p, sl);
     cplx<T> acc[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = {0, 0};
-    if (active) {
+    DirIn<T> dir{&a, 0};
+    DirIn<T> *const d = CG == CG_DIR_IN ? &dir : nullptr;
+    if (active || CG == CG_DIR_IN) {
         constexpr bool LNT = (NTM & 2) != 0;
         switch (w) {
-            case 0: hop_direction<0, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, acc); break;
-            case 1: hop_direction<1, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, acc); break;
-            case 2: hop_direction<2, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, acc); break;
-            default: hop_direction<3, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, s, c, acc, a.face); break;
+            case 0: hop_direction<0, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, acc, nullptr, d); break;
+            case 1: hop_direction<1, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, acc, nullptr, d); break;
+            case 2: hop_direction<2, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, acc, nullptr, d); break;
+            default: hop_direction<3, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, sl, c, acc, a.face, d); break;
         }
     }
     if (w > 0) {
@@ -299,6 +334,14 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     if (NORM == 2 && w == 1) {
         const double t = cg_alpha_of(a);
         if (lane == 0) alpha = t;
+    }
+    if constexpr (CG == CG_DIR_Y) {
+        if (w == 1 && active) cg_step_x<P>(a, s);
+        if (w == 2 && active) {
+            cplx<T> v[12];
+            cg_new_p<P>(a, p, s, v);
+            store_spinor<P>(a.p_new, s, v);
+        }
     }
     if (CG == CG_PRE && w == 3) cg_presum(a);
     __syncthreads();
@@ -311,7 +354,7 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         if constexpr (CG >= CG_RESID)
             cg_residual<P, CG - CG_RESID>(a, p, s, acc, nrm);
         else if constexpr (std::is_void<CT>::value)
-            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0, CG == CG_DIR_Y>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(part), "the tile fits the staging");
@@ -559,20 +602,23 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     const int64_t s = hop_site_index(a, lane, p, blk);
     const Geom &g = a.g;
     const bool active = s < g.vh;
-    // (coordinates of a padding site are never used, and s < 2^31 anyway)
-    const Coord c = cb_coords(g, p, s);
-    if (active) {
+    // (as in the 4-way shape)
+    const int64_t sl = CG == CG_DIR_IN && !active ? g.vh - 1 : s;
+    const Coord c = cb_coords(g, p, sl);
+    DirIn<T> dir{&a, 0};
+    DirIn<T> *const d = CG == CG_DIR_IN ? &dir : nullptr;
+    if (active || CG == CG_DIR_IN) {
         cplx<T> x0[3], x1[3];
         constexpr bool LNT = (NTM & 2) != 0;
         switch (w) {
-            case 0: hop_single<0, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 1: hop_single<1, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 2: hop_single<2, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 3: hop_single<3, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 4: hop_single<4, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 5: hop_single<5, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, x0, x1); break;
-            case 6: hop_single<6, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, s, c, x0, x1, a.face); break;
-            default: hop_single<7, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, s, c, x0, x1, a.face); break;
+            case 0: hop_single<0, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 1: hop_single<1, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 2: hop_single<2, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 3: hop_single<3, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 4: hop_single<4, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 5: hop_single<5, P, LK, DAG, LNT>(g, a.in[p], a.U, p, sl, c, x0, x1, nullptr, d); break;
+            case 6: hop_single<6, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, sl, c, x0, x1, a.face, d); break;
+            default: hop_single<7, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, sl, c, x0, x1, a.face, d); break;
         }
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -584,6 +630,14 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     if (NORM == 2 && w == 1) {
         const double t = cg_alpha_of(a);
         if (lane == 0) alpha = t;
+    }
+    if constexpr (CG == CG_DIR_Y) {
+        if (w == 1 && active) cg_step_x<P>(a, s);
+        if (w == 2 && active) {
+            cplx<T> v[12];
+            cg_new_p<P>(a, p, s, v);
+            store_spinor<P>(a.p_new, s, v);
+        }
     }
     if (CG == CG_PRE && w == 7) cg_presum(a);
     __syncthreads();
@@ -614,7 +668,7 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         add_staged<6, P, DAG>(chi, lane, acc);
         add_staged<7, P, DAG>(chi, lane, acc);
         if constexpr (std::is_void<CT>::value)
-            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0, CG == CG_DIR_Y>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(chi), "the tile fits the staging");
@@ -648,6 +702,15 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
             LQCD_RESID(LQCD_F32)
             LQCD_RESID(LQCD_F16)
 #undef LQCD_RESID
+        }
+    }
+    // (small lattices: their links stay cached)
+    if constexpr (P != LQCD_F16 && !DAG && !HALO && NTM < 2 && (HASY ? NORM == 1 : NORM == 0)) {
+        constexpr int role = HASY ? CG_DIR_Y : CG_DIR_IN;
+        if (a.cg == role) {
+            if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role><<<grid, 512, 0, st>>>(a);
+            else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, role><<<grid, 256, 0, st>>>(a);
+            return;
         }
     }
     if constexpr (DAG && !HASY && !NORM && !HALO) {
@@ -817,7 +880,11 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     a.nblk = grid.x;
     const bool hasy = a.y[0] != nullptr || a.y[1] != nullptr;
     const int norm = a.cg == CG_UPDATE ? 2 : a.partial != nullptr ? 1 : 0;
-    if (a.cg != CG_NONE && a.cg < CG_RESID && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
+    const bool dir = a.cg == CG_DIR_IN || a.cg == CG_DIR_Y;
+    if (dir && (prec == LQCD_F16 || dag || !a.sums || !a.sc || !a.p_old || (a.stream & 2))) return LQCD_EINVAL;
+    if (a.cg == CG_DIR_IN && (hasy || norm)) return LQCD_EINVAL;
+    if (a.cg == CG_DIR_Y && (!hasy || norm != 1 || !a.p_new || !a.x || a.p_new == a.p_old)) return LQCD_EINVAL;
+    if ((a.cg == CG_PRE || a.cg == CG_UPDATE) && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
     if (a.cg >= CG_RESID && (prec != LQCD_F64 || !dag || !hasy || norm != 1 || !a.rhs || !a.stored))
         return LQCD_EINVAL;
     if (a.cg == CG_UPDATE && (!hasy || !a.partial)) return LQCD_EINVAL;

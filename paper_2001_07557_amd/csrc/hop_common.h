@@ -128,11 +128,17 @@ __host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t
 // CG_GROUPS sums which the hop launch before it (CG_PRE) makes of them on the
 // side, one run of them per block of its first blocks: no launch in between,
 // and every sum in a fixed order.
+// CG_DIR_IN and CG_DIR_Y: small lattices, where an iteration is four launches
+// of a few microseconds, have no launch for the direction update.  The first
+// hop reads r and the old p and forms p = r + beta p at every neighbour (the
+// caches hold both), beta from the |r|^2 partials, which every wave sums; the
+// second forms p at its own sites once more, with the same bits, stores it
+// for the next iteration, and does x += alpha p old.
 // CG_RESID + P: the FP64 adjoint hop that completes A x of a reliable update:
 // the epilogue forms r = rhs - A x, leaves the block partials of |r|^2, rounds
 // r to the inner precision P, stores it as the inner residual and leaves the
 // partials of |r as stored|^2.
-enum { CG_NONE = 0, CG_PRE, CG_UPDATE, CG_RESID };
+enum { CG_NONE = 0, CG_PRE, CG_UPDATE, CG_DIR_IN, CG_DIR_Y, CG_RESID };
 constexpr int CG_GROUPS = 128;
 // the solver's device scalars: the residual |r|^2 of the even and of the odd
 // iterations (an iteration reads the one before's), alpha, beta, and a value
@@ -198,8 +204,12 @@ struct HopArgs {
     // CG_RESID: right-hand side, and the partials of |r|^2 as stored
     const char *rhs;
     double *stored;
+    // CG_DIR_IN, CG_DIR_Y: the old direction, the new one, and x
+    const char *p_old;
+    char *p_new, *x;
     int cg;               // role of the launch
     int slot;             // parity of the iteration (CG_RR)
+    int restart;          // CG_DIR_IN: beta = 0
     // host side: dynamic LDS bytes added to each 4-way block (limits the
     // blocks in flight per CU; not read by the kernels)
     uint32_t lds_extra;
@@ -791,6 +801,43 @@ __device__ __forceinline__ int64_t hop_neighbour(const Geom &g, int64_t s, const
     }
 }
 
+// beta of this iteration (CG_DIR_IN), summed by every wave; thread 0 of the
+// launch keeps it.
+__device__ __forceinline__ double cg_beta_of(const HopArgs &a) {
+    const double rr = wave_total(a.sums, a.n_sums);
+    const double old = a.sc[CG_RR + (a.slot ^ 1)];
+    const double b = old > 0.0 && !a.restart ? rr / old : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.sc[CG_RR + a.slot] = rr;
+        a.sc[CG_BETA] = b;
+    }
+    return b;
+}
+
+// The input of a hop: the field `in`, or (D not null) r + beta p from in = r
+// and the old p, beta formed (FIRST) while the words are on their way.
+template <typename T>
+struct DirIn {
+    const HopArgs *a;
+    T beta;
+};
+template <int P, bool FIRST>
+__device__ __forceinline__ void load_hop_in(const char *__restrict__ in, int64_t s,
+                                            cplx<typename hop_elem<P>::type> v[12],
+                                            typename real_of<P>::type &factor,
+                                            DirIn<typename real_of<P>::type> *d) {
+    load_spinor_hop<P>(in, s, v, factor);
+    if constexpr (P != LQCD_F16) {
+        if (d) {
+            cplx<typename real_of<P>::type> vp[12];
+            load_spinor<P>(d->a->p_old, s, vp);
+            if (FIRST) d->beta = (typename real_of<P>::type)cg_beta_of(*d->a);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) v[k] = {fmad(d->beta, vp[k].re, v[k].re), fmad(d->beta, vp[k].im, v[k].im)};
+        }
+    }
+}
+
 // chi of the single hop H (0..7: direction H/2, forward for even H) of site s.
 // HALO: the t-hops that cross the t boundary take their half-spinor (forward)
 // or its product with U^dag (backward) from the face buffers.
@@ -799,7 +846,8 @@ __device__ __forceinline__ void hop_single(const Geom &g, const char *__restrict
                                            const char *__restrict__ U, int p, int64_t s,
                                            const Coord &c, cplx<typename real_of<P>::type> x0[3],
                                            cplx<typename real_of<P>::type> x1[3],
-                                           const char *const *face = nullptr) {
+                                           const char *const *face = nullptr,
+                                           DirIn<typename real_of<P>::type> *dir = nullptr) {
     using T = typename real_of<P>::type;
     constexpr int MU = H >> 1;
     constexpr bool FWD = (H & 1) == 0;
@@ -842,7 +890,7 @@ __device__ __forceinline__ void hop_single(const Geom &g, const char *__restrict
     const int64_t nb = hop_neighbour<MU, FWD>(g, s, c, flip);
     cplx<typename hop_elem<P>::type> psi[12];
     T sgn = flip ? T(-1) : T(1);
-    load_spinor_hop<P>(in, nb, psi, sgn);
+    load_hop_in<P, true>(in, nb, psi, sgn, dir);
     link_chi<MU, S, !FWD, P, LK, LNT>(U, g.ntiles, FWD ? p : p ^ 1, FWD ? s : nb, psi, sgn, x0, x1);
 }
 
@@ -862,7 +910,8 @@ template <int MU, int P, int LK, bool DAG, bool LNT, bool HALO = false>
 __device__ __forceinline__ void hop_direction(const Geom &g, const char *__restrict__ in,
                                               const char *__restrict__ U, int p, int64_t s,
                                               const Coord &c, cplx<typename real_of<P>::type> acc[12],
-                                              const char *const *face = nullptr) {
+                                              const char *const *face = nullptr,
+                                              DirIn<typename real_of<P>::type> *dir = nullptr) {
     using T = typename real_of<P>::type;
     using PR = Proj<MU>;
     constexpr int SF = DAG ? 1 : -1;
@@ -895,7 +944,7 @@ __device__ __forceinline__ void hop_direction(const Geom &g, const char *__restr
     } else {
         T sgn = flip_f ? T(-1) : T(1);
         cplx<typename hop_elem<P>::type> psi[12];
-        load_spinor_hop<P>(in, fwd, psi, sgn);
+        load_hop_in<P, true>(in, fwd, psi, sgn, dir);
         link_chi<MU, SF, false, P, LK, LNT>(U, g.ntiles, p, s, psi, sgn, f, f + 3);
     }
     hop_fence<T, 6>(f);
@@ -910,7 +959,7 @@ __device__ __forceinline__ void hop_direction(const Geom &g, const char *__restr
         } else {
             T sgn = flip_b ? T(-1) : T(1);
             cplx<typename hop_elem<P>::type> psi[12];
-            load_spinor_hop<P>(in, bwd, psi, sgn);
+            load_hop_in<P, false>(in, bwd, psi, sgn, dir);
             link_chi<MU, SB, true, P, LK, LNT, P != LQCD_F16>(U, g.ntiles, p ^ 1, bwd, psi, sgn, b, b + 3);
             if constexpr (P == LQCD_F16) fb = sgn;
         }
