@@ -24,7 +24,9 @@
  *    DEVICE memory owned by the caller.  The library never allocates, frees
  *    or retains device memory and keeps no global state besides the HIP
  *    module, whose one static device array (the scratch of
- *    lqcd_dot_noalloc) comes with it.  Host pointers are named so
+ *    lqcd_dot_noalloc) comes with it.  The solver keeps one 4 KiB page
+ *    of pinned host memory per process, through which kernels hand it
+ *    numbers.  Host pointers are named so
  *    explicitly (stats, result).
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *    Every call is enqueued on it and returns without waiting, except where

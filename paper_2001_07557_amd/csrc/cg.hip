@@ -33,6 +33,7 @@
 #include "reduce.h"
 #include "hop_common.h"
 #include "blas.h"
+#include "mail.h"
 
 namespace lqcd {
 
@@ -77,14 +78,26 @@ __device__ __forceinline__ double partial_total(const double *partial, int n, in
     return total;
 }
 
-// The sum for the host.  RESID: the sum of a recomputed residual, after which
-// x has no step pending.
+// The sum (and that of a second run of n, if given) for the host, posted or
+// (no mail) left for a copy.  RESID: the sum of a recomputed residual, after
+// which x has no step pending.
 template <bool RESID>
-__global__ __launch_bounds__(SUM_BLOCK) void cg_sum_k(const double *partial, int n, int stride, double *sc) {
+__global__ __launch_bounds__(SUM_BLOCK) void cg_sum_k(const double *partial, const double *second, int n,
+                                                      int stride, double *sc, Mail *mail, uint64_t count) {
     const double s = partial_total(partial, n, stride);
+    double t = 0.0;
+    if (second) {
+        __syncthreads();
+        t = partial_total(second, n, stride);
+    }
     if (threadIdx.x == 0) {
-        sc[CG_OUT] = s;
         if (RESID) sc[CG_ALPHA] = 0.0;
+        if (mail) {
+            mail_post(mail, count, s, t);
+        } else {
+            sc[CG_OUT] = s;
+            sc[CG_OUT + 1] = t;
+        }
     }
 }
 
@@ -237,13 +250,13 @@ static CGWork cg_layout(const Geom &g, int prec, char *base) {
     // the FP64 temporaries' place, which are its own
     char *scratch = take(hb64);
     char *t64[2] = {take(hb64), take(hb64)};
-    const int64_t tiles = hop_partials(g, 1), norms = 2 * reduce_blocks(g, 1);
-    w.partial = (double *)take(sizeof(double) * (tiles > norms ? tiles : norms));
+    const int64_t tiles = hop_partials(g, 1), norms = 4 * reduce_blocks(g, 1);
+    w.partial = (double *)take(sizeof(double) * tiles);
     w.sc = (double *)take(sizeof(double) * CG_SCALARS);
     if (base) {
         w.groups = (double *)scratch;
         w.pap = w.groups + CG_GROUPS;
-        // (sums: at most 128 + V/64 doubles of the 1536 per tile)
+        // (sums: at most 128 + 4 per tile of the 1536 doubles per tile)
         w.p[1] = prec == LQCD_F64 ? t64[0]
                                   : scratch + align256(sizeof(double) * (CG_GROUPS + (tiles > norms ? tiles : norms)));
         w.te64 = prec == LQCD_F64 ? w.te : t64[0];
@@ -306,6 +319,8 @@ struct Solver {
     int link64;
     const char *U64;
     CGWork w;
+    MailSlot mail;
+
     int hop(int out_par, char *out, const char *in, const char *y, double alpha, bool dag, int pr,
             int lk, const char *U_, double *partial, int cg = CG_NONE, int slot = 0, const char *rhs = nullptr,
             bool restart = false) {
@@ -374,8 +389,16 @@ struct Solver {
 
     dim3 grid() const { return dim3((unsigned)((g.vh + CG_BLOCK - 1) / CG_BLOCK)); }
 
-    int read(double *host, int slot) {
-        hipError_t e = hipMemcpyAsync(host, w.sc + slot, sizeof(double), hipMemcpyDeviceToHost, st);
+    // the sums of n partials, and of n more (second), on the host
+    template <bool RESID>
+    int total(const double *partial, int n, int stride, double *host, const double *second = nullptr) {
+        const int nv = second ? 2 : 1;
+        cg_sum_k<RESID><<<1, SUM_BLOCK, 0, st>>>(partial, second, n, stride, w.sc, mail.get(),
+                                                 mail.get() ? mail.next() : 0);
+        const int rc = check_launch();
+        if (rc) return rc;
+        if (mail.get()) return mail.wait(st, host, nv);
+        hipError_t e = hipMemcpyAsync(host, w.sc + CG_OUT, nv * sizeof(double), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             set_hip_error(e);
@@ -384,18 +407,12 @@ struct Solver {
         return LQCD_OK;
     }
 
-    // |v|^2 of an FP64 half field on the host
-    int norm64(const char *v, double *host) {
-        launch_reduce(g, 1, v, nullptr, LQCD_F64, w.pap, st);
-        return total<false>(w.pap, (int)reduce_blocks(g, 1), 2, host);
-    }
-
-    // the sum of n partials on the host
-    template <bool RESID>
-    int total(const double *partial, int n, int stride, double *host) {
-        cg_sum_k<RESID><<<1, SUM_BLOCK, 0, st>>>(partial, n, stride, w.sc);
-        const int rc = check_launch();
-        return rc ? rc : read(host, CG_OUT);
+    // |a|^2 and |b|^2 of two FP64 half fields on the host
+    int norms64(const char *a, const char *b, double host[2]) {
+        const int n = (int)reduce_blocks(g, 1);
+        launch_reduce(g, 1, a, nullptr, LQCD_F64, w.pap, st);
+        launch_reduce(g, 1, b, nullptr, LQCD_F64, w.pap + 2 * n, st);
+        return total<false>(w.pap, n, 2, host, w.pap + 2 * n);
     }
 
     // The inner residual from the true one: rs = b - A64 x64 (FP64, rounded to
@@ -415,9 +432,11 @@ struct Solver {
             lqcd_cg_stats_t *stats) {
         stats->iterations = 0;
         stats->reliable_updates = 0;
-        double bb = 0.0;
-        int rc = norm64(b, &bb);
+        mail.open();
+        double norms[2] = {0.0, 0.0};
+        int rc = norms64(b, x64, norms);
         if (rc) return rc;
+        const double bb = norms[0], xx = norms[1];
         if (!std::isfinite(bb)) return LQCD_ENAN;
         if (bb == 0.0) {
             // the solution of A x = 0 is x = 0
@@ -434,9 +453,6 @@ struct Solver {
         double rr = 0.0;
         // a zero starting guess (the common case) needs no FP64 operator
         // application: r = b
-        double xx = 0.0;
-        rc = norm64(x64, &xx);
-        if (rc) return rc;
         if (xx == 0.0) rr = bb;
         else rc = true_residual<P>(x64, b, &rr);
         if (rc) return rc;

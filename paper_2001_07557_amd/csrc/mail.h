@@ -1,0 +1,49 @@
+// Numbers for the host without a copy: a kernel writes them into a slot of
+// pinned host memory and the host, which has nothing else to do meanwhile,
+// watches the slot's count.  An 8-byte copy to pageable memory is a launch of
+// its own and a wait for its completion, 20-25 us in which the GPU idles; a
+// posted value arrives 2-3 us after the kernel's end.
+//
+// One 4 KiB page per process, allocated at the first use and kept (64 slots,
+// each given out to one call at a time and handed back at its end); a call
+// that finds no slot, or no page, copies as before.
+#pragma once
+
+#include "lqcd_internal.h"
+
+namespace lqcd {
+
+struct alignas(64) Mail {
+    uint64_t count;  // posts so far: the value of the last one is complete
+    double v[2];
+};
+
+// A slot for one call and stream, given back at its end; get() is NULL before
+// open() and where there is none.
+class MailSlot {
+public:
+    MailSlot() = default;
+    ~MailSlot();
+    void open();
+    MailSlot(const MailSlot &) = delete;
+    MailSlot &operator=(const MailSlot &) = delete;
+    Mail *get() const { return m_; }
+    // the number of the next post
+    uint64_t next() { return ++n_; }
+    // waits for the post numbered last by next(), made by a kernel on st
+    int wait(hipStream_t st, double *out, int nv);
+
+private:
+    Mail *m_ = nullptr;
+    uint64_t n_ = 0;
+    int slot_ = -1;
+};
+
+// One thread of the grid posts v[0..1].
+__device__ __forceinline__ void mail_post(Mail *m, uint64_t count, double a, double b) {
+    __hip_atomic_store(&m->v[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&m->v[1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&m->count, count, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+}  // namespace lqcd

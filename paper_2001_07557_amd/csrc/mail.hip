@@ -1,0 +1,69 @@
+// Slots of pinned host memory that kernels post numbers into (mail.h).
+
+#include <mutex>
+
+#include "mail.h"
+
+namespace lqcd {
+
+constexpr int MAIL_SLOTS = 64;
+static std::mutex mail_mutex;
+static Mail *mail_page = nullptr;
+static uint64_t mail_used = 0;  // a bit per slot
+static_assert(MAIL_SLOTS * sizeof(Mail) == 4096, "one page");
+
+void MailSlot::open() {
+    std::lock_guard<std::mutex> lock(mail_mutex);
+    if (!mail_page) {
+        // (allowed while another thread captures a graph)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, MAIL_SLOTS * sizeof(Mail),
+                                           hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        mail_page = static_cast<Mail *>(p);
+    }
+    for (int i = 0; i < MAIL_SLOTS; ++i)
+        if (!((mail_used >> i) & 1)) {
+            mail_used |= (uint64_t)1 << i;
+            slot_ = i;
+            m_ = mail_page + i;
+            n_ = __atomic_load_n(&m_->count, __ATOMIC_ACQUIRE);
+            return;
+        }
+}
+
+MailSlot::~MailSlot() {
+    if (slot_ < 0) return;
+    std::lock_guard<std::mutex> lock(mail_mutex);
+    mail_used &= ~((uint64_t)1 << slot_);
+}
+
+int MailSlot::wait(hipStream_t st, double *out, int nv) {
+    hipError_t e = hipErrorNotReady;
+    for (uint32_t spin = 1; __atomic_load_n(&m_->count, __ATOMIC_ACQUIRE) != n_; ++spin) {
+        if (e == hipSuccess) {
+            // the stream has drained and nothing was posted
+            set_hip_error(hipErrorUnknown);
+            return LQCD_EHIP;
+        }
+        __builtin_ia32_pause();
+        if (spin % 4096 == 0) {
+            e = hipStreamQuery(st);
+            if (e == hipErrorNotReady) (void)hipGetLastError();
+            else if (e != hipSuccess) {
+                set_hip_error(e);
+                return LQCD_EHIP;
+            }
+        }
+    }
+    for (int i = 0; i < nv; ++i) __atomic_load(&m_->v[i], &out[i], __ATOMIC_RELAXED);
+    return LQCD_OK;
+}
+
+}  // namespace lqcd

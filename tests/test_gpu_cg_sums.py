@@ -42,3 +42,38 @@ def test_solve_at_the_edges_of_the_sums(dims, prec):
     P.axpby(0.999, x, 0.0, mx)
     st2 = P.cg_solve(mx, b, hi, lo, kappa, tol=tol)
     assert st2.true_residual <= tol and 0 < st2.iterations <= st.iterations
+
+
+def test_solves_on_threads_and_streams():
+    """Solves that run at once, each on its own thread and stream, get their
+    own sums: the bits of the same solve alone."""
+    import threading
+
+    import torch
+    dims, kappa, jobs = (8, 8, 8, 8), 0.12, 4
+    lat = P.Lattice(dims)
+
+    def solve(seed):
+        U, psi = LI.workload_fields_device(seed, dims, "cuda")
+        hi, lo = P.pack_gauge(lat, U, P.F64, 12), P.pack_gauge(lat, U, P.F32, 12)
+        b, x = P.pack_spinor(lat, psi, P.F64, P.EVEN), P.new_spinor(lat, P.F64, P.EVEN)
+        st = P.cg_solve(x, b, hi, lo, kappa)
+        return st.iterations, st.true_residual, x.buf.cpu()
+
+    alone = [solve(20 + i) for i in range(jobs)]
+    got = [[] for _ in range(2 * jobs)]
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(3):
+                got[i].append(solve(20 + i % jobs))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2 * jobs)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i, results in enumerate(got):
+        assert len(results) == 3
+        for n, res, x in results:
+            assert (n, res) == alone[i % jobs][:2] and torch.equal(x, alone[i % jobs][2])
