@@ -141,15 +141,35 @@ __global__ __launch_bounds__(256) void split_rotate_wave_k(E *out, const E *in, 
     if (i < n) out[i] = y;
 }
 
-// split_rotate, any VL: each lane gathers its source element.
+// split_rotate, any VL: each lane gathers its source elements, ROT_PER of
+// them, ROT_BLOCK apart.  The vector index of a block's first element is one
+// 64-bit division per block; from there 32-bit multiply-and-shift divisions.
+// Vectors of 256 doubles, 25 M elements: 81.3 -> 71.3 us (5.7 TB/s) against
+// one element per thread by 64-bit remainders.
+constexpr int ROT_BLOCK = 256, ROT_PER = 4;
 template <typename E>
-__global__ __launch_bounds__(256) void split_rotate_gather_k(E *out, const E *in, int64_t n,
-                                                             int vl, int w, int r) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t base = i - i % vl;
-    const int e = (int)(i - base);
-    out[i] = in[base + (e / w) * w + (e % w + r) % w];
+__global__ __launch_bounds__(ROT_BLOCK) void split_rotate_gather_k(E *out, const E *in, int64_t n,
+                                                                   FastDiv vl, FastDiv w, int r) {
+    const int64_t b0 = (int64_t)blockIdx.x * (ROT_BLOCK * ROT_PER);
+    const uint32_t off = (uint32_t)(b0 % vl.d);  // the block starts inside a vector
+    const int left = n - b0 < ROT_BLOCK * ROT_PER ? (int)(n - b0) : ROT_BLOCK * ROT_PER;
+    const E *src = in + b0;
+    E v[ROT_PER];
+#pragma unroll
+    for (int j = 0; j < ROT_PER; ++j) {
+        const int k = j * ROT_BLOCK + (int)threadIdx.x;
+        const uint32_t at = off + (uint32_t)k;
+        const uint32_t e = at - fdiv(at, vl) * vl.d;  // element of its vector
+        const uint32_t c = e - fdiv(e, w) * w.d;      // and of its run of w
+        const uint32_t t = c + (uint32_t)r;
+        const int64_t d = (int64_t)k + (int64_t)(t >= w.d ? t - w.d : t) - (int64_t)c;
+        if (k < left) v[j] = src[d];
+    }
+#pragma unroll
+    for (int j = 0; j < ROT_PER; ++j) {
+        const int k = j * ROT_BLOCK + (int)threadIdx.x;
+        if (k < left) out[b0 + k] = v[j];
+    }
 }
 
 }  // namespace lqcd
@@ -199,12 +219,17 @@ extern "C" int lqcd_split_rotate(void *out, const void *in, int64_t nvec, int vl
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     hipStream_t st = (hipStream_t)stream;
     const bool in_wave = 64 % vl == 0;
+    // (off + k < 2^31 + 1024 would leave the 31 bits of fdiv only for vectors
+    // of more than 2^31 - 1024 elements)
+    if (!in_wave && vl > 0x7fffffff - ROT_BLOCK * ROT_PER) return LQCD_EINVAL;
+    const dim3 gather((unsigned)((n + ROT_BLOCK * ROT_PER - 1) / (ROT_BLOCK * ROT_PER)));
+    const FastDiv dv = make_fastdiv((uint32_t)vl), dw = make_fastdiv((uint32_t)w);
     if (elem_bytes == 8) {
         if (in_wave) split_rotate_wave_k<double><<<grid, block, 0, st>>>((double *)out, (const double *)in, n, vl, w, rr);
-        else split_rotate_gather_k<double><<<grid, block, 0, st>>>((double *)out, (const double *)in, n, vl, w, rr);
+        else split_rotate_gather_k<double><<<gather, block, 0, st>>>((double *)out, (const double *)in, n, dv, dw, rr);
     } else {
         if (in_wave) split_rotate_wave_k<double2><<<grid, block, 0, st>>>((double2 *)out, (const double2 *)in, n, vl, w, rr);
-        else split_rotate_gather_k<double2><<<grid, block, 0, st>>>((double2 *)out, (const double2 *)in, n, vl, w, rr);
+        else split_rotate_gather_k<double2><<<gather, block, 0, st>>>((double2 *)out, (const double2 *)in, n, dv, dw, rr);
     }
     return check_launch();
 }
