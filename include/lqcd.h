@@ -24,7 +24,7 @@
  *    DEVICE memory owned by the caller.  The library never allocates, frees
  *    or retains device memory and keeps no global state besides the HIP
  *    module, whose one static device array (the scratch of
- *    lqcd_dot_noalloc) comes with it.  The solver keeps one 4 KiB page
+ *    lqcd_dot_noalloc) comes with it.  The solver and the reductions keep one 4 KiB page
  *    of pinned host memory per process, through which kernels hand it
  *    numbers.  Host pointers are named so
  *    explicitly (stats, result).

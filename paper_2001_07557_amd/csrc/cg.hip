@@ -409,7 +409,7 @@ struct Solver {
 
     // |a|^2 and |b|^2 of two FP64 half fields on the host
     int norms64(const char *a, const char *b, double host[2]) {
-        const int n = (int)reduce_blocks(g, 1);
+        const int n = (int)reduce_grid(g, 1);
         launch_reduce(g, 1, a, nullptr, LQCD_F64, w.pap, st);
         launch_reduce(g, 1, b, nullptr, LQCD_F64, w.pap + 2 * n, st);
         return total<false>(w.pap, n, 2, host, w.pap + 2 * n);
