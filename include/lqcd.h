@@ -300,7 +300,7 @@ size_t lqcd_cg_workspace_bytes(const lqcd_geom_t *g, int inner_prec, int inner_l
  *   fifth (the recurrence has drifted: the direction restarts from the
  *   residual as well); it is taken every `reliable_every` iterations (0 =
  *   never on a schedule), whenever the inner residual has fallen since the
- *   last update by 1000x (FP32 inner) or 10x (F16 inner), beyond which the
+ *   last update by 10000x (FP32 inner) or 10x (F16 inner), beyond which the
  *   inner recurrence is not trusted (for FP32 inner iterations put off, by
  *   at most a further 100x fall, while the decay so far puts the tolerance
  *   within ten iterations, when the final update comes first),

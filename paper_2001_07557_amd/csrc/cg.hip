@@ -43,11 +43,14 @@ constexpr int CHECK_EVERY = 10;
 // within a factor delta of the last true residual: past that point the
 // computed and true residuals part (rounding of the inner precision), so a
 // reliable update is taken.  delta = 0.1 for binary16 storage (unit roundoff
-// 2^-11), 1e-3 for FP32 (2^-24: after a 1000-fold drop the rounding carried
-// by the recurrence is still ~1e-3 of the residual); FP64 inner iterations
-// need it only at the end.
+// 2^-11), 1e-4 for FP32 (2^-24: after that drop the rounding carried by the
+// recurrence is a few 1e-3 of the residual); FP64 inner iterations need it
+// only at the end.  FP32 inner to 1e-10, iterations / updates with delta =
+// 1e-3, 1e-4, 1e-5: 24^3x48 links spread by 0.3 around one 46/3, 46/2, 48/2
+// (8.64, 8.30, 8.61 ms), by 0.15 105/4, 105/4, 106/3, Haar links 24/3, 24/2,
+// 27/2; to 1e-12 1e-3 and 1e-4 take the same or one update less.
 constexpr double DELTA_F16 = 0.1;
-constexpr double DELTA_F32 = 1e-3;
+constexpr double DELTA_F32 = 1e-4;
 // A reduced-precision recurrence residual runs ahead of the true one, so the
 // final reliable update is taken when it reaches tol / 2 rather than tol
 // (squared: 0.25): an update taken when the recurrence first touches tol
