@@ -105,21 +105,35 @@ constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #endif
 constexpr int64_t INFINITY_CACHE_BYTES = (int64_t)256 << 20;
 
-// acc = alpha acc + beta y (DIR: y is the new direction).  The fused product is spelled out, so that every
-// instance rounds alike (the compiler may fuse either one).
 template <int P>
 __device__ __forceinline__ void cg_new_p(const HopArgs &a, int p, int64_t s,
                                          cplx<typename real_of<P>::type> v[12]);
 
-template <int P, bool HASY, bool DIR = false>
-__device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
+// What the epilogue of a site adds (DIR: y is the new direction).  Launches
+// whose links are streamed (NTM bit 1: even-odd, beyond the Infinity Cache),
+// FP64 and FP32, read it before the barrier that the epilogue waits at, so that
+// its latency passes meanwhile: Mhat 32^4 FP64-18 281.4 -> 278.7 us, 48^3x96
+// FP32-12 1163 -> 1154.  The others read it after: small launches lose by it
+// (Mhat 16^4 FP32-12 10.60 -> 10.76 us, also with a switch at run time),
+// binary16 ones too (32^4 solve 9.29 -> 9.37 ms), and CG_UPDATE needs the
+// registers (24^3x48 FP32 solve 8.23 -> 8.25 ms).
+template <int P, int NORM, int NTM>
+constexpr bool early_y() { return (NTM & 2) != 0 && P != LQCD_F16 && NORM != 2; }
+template <int P, bool HASY, bool DIR>
+__device__ __forceinline__ void load_y(const HopArgs &a, int p, int64_t s,
+                                       cplx<typename real_of<P>::type> y[12]) {
+    if constexpr (DIR) cg_new_p<P>(a, p, s, y);
+    else if constexpr (HASY) load_spinor<P>(a.y[p], s, y);
+}
+
+// acc = alpha acc + beta y.  The fused product is spelled out, so that every
+// instance rounds alike (the compiler may fuse either one).
+template <int P, bool HASY>
+__device__ __forceinline__ void hop_combine(const HopArgs &a, const cplx<typename real_of<P>::type> y[12],
                                             cplx<typename real_of<P>::type> acc[12]) {
     using T = typename real_of<P>::type;
     const T alpha = (T)a.alpha;
     if constexpr (HASY) {
-        cplx<T> y[12];
-        if constexpr (DIR) cg_new_p<P>(a, p, s, y);
-        else load_spinor<P>(a.y[p], s, y);
         const T beta = (T)a.beta;
 #pragma unroll
         for (int k = 0; k < 12; ++k)
@@ -136,12 +150,13 @@ __device__ __forceinline__ void hop_combine(const HopArgs &a, int p, int64_t s,
 // returns |r|^2 of the site.  x += alpha p waits for the pass that reads p
 // next anyway (the direction update): one vector less per iteration, and
 // fewer registers here.
-template <int P, bool HASY, int NORM, bool NT, bool DIR = false>
+template <int P, bool HASY, int NORM, bool NT>
 __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t s,
+                                               const cplx<typename real_of<P>::type> y[12],
                                                cplx<typename real_of<P>::type> acc[12],
                                                double cg_alpha = 0.0) {
     using T = typename real_of<P>::type;
-    hop_combine<P, HASY, DIR>(a, p, s, acc);
+    hop_combine<P, HASY>(a, y, acc);
     if constexpr (NORM == 2) {
         const T c = (T)cg_alpha;
         cplx<T> vr[12];
@@ -170,9 +185,10 @@ __device__ __forceinline__ double hop_epilogue(const HopArgs &a, int p, int64_t 
 // nrm = |r|^2 in FP64 and |r as stored|^2.
 template <int P, int PI>
 __device__ __forceinline__ void cg_residual(const HopArgs &a, int p, int64_t s,
+                                            const cplx<typename real_of<P>::type> y[12],
                                             cplx<typename real_of<P>::type> acc[12], double nrm[2]) {
     using TI = typename real_of<PI>::type;
-    hop_combine<P, true>(a, p, s, acc);
+    hop_combine<P, true>(a, y, acc);
     cplx<double> b[12];
     cplx<TI> r[12];
     load_spinor<LQCD_F64>(a.rhs, s, b);
@@ -240,11 +256,12 @@ __device__ __forceinline__ void cg_presum(const HopArgs &a) {
 // separate unpacking pass.
 template <typename CT, int P, bool HASY, int THREADS>
 __device__ __forceinline__ void hop_canon(const HopArgs &a, int p, int64_t s, bool mine,
+                                          const cplx<typename real_of<P>::type> y[12],
                                           cplx<typename real_of<P>::type> acc[12], v4u *stage) {
     constexpr int GS = spinor_granules<CT>();
     const int lane = threadIdx.x & 63;
     if (mine) {
-        hop_combine<P, HASY>(a, p, s, acc);
+        hop_combine<P, HASY>(a, y, acc);
         // the reads of the staged hops come before these writes of another type
         asm volatile("" ::: "memory");
         CT *d = reinterpret_cast<CT *>(stage + lane * (GS + 1));
@@ -344,21 +361,28 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
         }
     }
     if (CG == CG_PRE && w == 3) cg_presum(a);
+    cplx<T> y[12];
+    constexpr bool early = early_y<P, NORM, NTM>();
+    if (early && w == 0 && active) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
     __syncthreads();
+    // (FP64: before the LDS sums, M 32^4 FP64-12 193.4 -> 191.3 us)
+    constexpr bool first_y = P == LQCD_F64 && CG != CG_DIR_Y;
     double nrm[2] = {0.0, 0.0};
     if (w == 0 && active) {
+        if (!early && first_y) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[j][k][lane];
+        if (!early && !first_y) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
         if constexpr (CG >= CG_RESID)
-            cg_residual<P, CG - CG_RESID>(a, p, s, acc, nrm);
+            cg_residual<P, CG - CG_RESID>(a, p, s, y, acc, nrm);
         else if constexpr (std::is_void<CT>::value)
-            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0, CG == CG_DIR_Y>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, y, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(part), "the tile fits the staging");
-        hop_canon<CT, P, HASY, 256>(a, p, s, w == 0 && active, acc, reinterpret_cast<v4u *>(part));
+        hop_canon<CT, P, HASY, 256>(a, p, s, w == 0 && active, y, acc, reinterpret_cast<v4u *>(part));
     }
     if constexpr (NORM) {
         // wave 0 holds every site of the tile: a wave reduction suffices and
@@ -480,7 +504,9 @@ __global__ __launch_bounds__(256) void hop4t_kernel(HopArgs a) {
             for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int k = 0; k < 12; ++k) acc[k] = acc[k] + part[q][k][lane];
-            const double nrm = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc,
+            cplx<T> y[12];
+            load_y<P, HASY, false>(a, p, s, y);
+            const double nrm = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, y, acc,
                                                                            NORM == 2 ? cg_alpha_of(a) : 0.0);
             if constexpr (NORM != 0) {
                 const double tot = wave_sum(nrm);
@@ -519,7 +545,8 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
         hop_direction<3, P, LK, DAG, LNT, HALO>(g, a.in[p], a.U, p, s, c, d, a.face);
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = acc[k] + d[k];
-        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, acc, NORM == 2 ? cg_alpha_of(a) : 0.0);
+        load_y<P, HASY, false>(a, p, s, d);
+        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, d, acc, NORM == 2 ? cg_alpha_of(a) : 0.0);
     }
     if constexpr (NORM) {
         const double t = wave_sum(nrm[0]);
@@ -640,6 +667,9 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         }
     }
     if (CG == CG_PRE && w == 7) cg_presum(a);
+    cplx<T> y[12];
+    constexpr bool early = early_y<P, NORM, NTM>();
+    if (early && w == 0 && active) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
     __syncthreads();
     if constexpr (ROWS) {
         static_assert(!HASY && !NORM, "the row-parallel rebuild has no y term and no norm");
@@ -667,12 +697,13 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
         add_staged<5, P, DAG>(chi, lane, acc);
         add_staged<6, P, DAG>(chi, lane, acc);
         add_staged<7, P, DAG>(chi, lane, acc);
+        if (!early) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
         if constexpr (std::is_void<CT>::value)
-            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0, CG == CG_DIR_Y>(a, p, s, acc, NORM == 2 ? alpha : 0.0);
+            nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, y, acc, NORM == 2 ? alpha : 0.0);
     }
     if constexpr (!std::is_void<CT>::value) {
         static_assert(canon_stage_bytes<spinor_granules<CT>()>() <= sizeof(chi), "the tile fits the staging");
-        hop_canon<CT, P, HASY, 512>(a, p, s, w == 0 && active, acc, reinterpret_cast<v4u *>(chi));
+        hop_canon<CT, P, HASY, 512>(a, p, s, w == 0 && active, y, acc, reinterpret_cast<v4u *>(chi));
     }
     if constexpr (NORM) {
         // wave 0 holds every site of the tile: a wave reduction suffices and
