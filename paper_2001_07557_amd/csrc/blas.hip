@@ -294,7 +294,7 @@ static int reduce_entry(const lqcd_geom_t *gg, int subset, const void *a, const 
     launch_reduce(g, nh, (const char *)a, (const char *)b, prec, partial, st);
 #else
     launch_reduce(g, nh, (const char *)a, (const char *)b, prec, partial, st);
-    if (post) mail.open();
+    if (post) mail.open(st);
     finalize_k<<<1, FIN_BLOCK, 0, st>>>(partial, reduce_grid(g, nh), out, mail.get(),
                                         mail.get() ? mail.next() : 0);
 #endif

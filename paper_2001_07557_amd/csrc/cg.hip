@@ -435,7 +435,7 @@ struct Solver {
             lqcd_cg_stats_t *stats) {
         stats->iterations = 0;
         stats->reliable_updates = 0;
-        mail.open();
+        mail.open(st);
         double norms[2] = {0.0, 0.0};
         int rc = norms64(b, x64, norms);
         if (rc) return rc;

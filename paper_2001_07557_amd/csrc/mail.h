@@ -19,12 +19,13 @@ struct alignas(64) Mail {
 };
 
 // A slot for one call and stream, given back at its end; get() is NULL before
-// open() and where there is none.
+// open(), where there is none, and on a stream that is being captured (whose
+// kernels do not run: the copy is refused there).
 class MailSlot {
 public:
     MailSlot() = default;
     ~MailSlot();
-    void open();
+    void open(hipStream_t st);
     MailSlot(const MailSlot &) = delete;
     MailSlot &operator=(const MailSlot &) = delete;
     Mail *get() const { return m_; }

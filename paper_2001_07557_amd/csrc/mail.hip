@@ -12,7 +12,13 @@ static Mail *mail_page = nullptr;
 static uint64_t mail_used = 0;  // a bit per slot
 static_assert(MAIL_SLOTS * sizeof(Mail) == 4096, "one page");
 
-void MailSlot::open() {
+void MailSlot::open(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (status != hipStreamCaptureStatusNone) return;
     std::lock_guard<std::mutex> lock(mail_mutex);
     if (!mail_page) {
         // (allowed while another thread captures a graph)

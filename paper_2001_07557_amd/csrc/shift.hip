@@ -159,7 +159,9 @@ __global__ __launch_bounds__(ROT_BLOCK) void split_rotate_gather_k(E *out, const
     for (int j = 0; j < ROT_PER; ++j) {
         const int k = j * ROT_BLOCK + (int)threadIdx.x;
         const uint32_t at = off + (uint32_t)k;
-        const uint32_t e = at - fdiv(at, vl) * vl.d;  // element of its vector
+        // element of its vector (a long vector ends at most once per block, and
+        // `at` may pass the 31 bits of fdiv there)
+        const uint32_t e = vl.d >= ROT_BLOCK * ROT_PER ? (at >= vl.d ? at - vl.d : at) : at - fdiv(at, vl) * vl.d;
         const uint32_t c = e - fdiv(e, w) * w.d;      // and of its run of w
         const uint32_t t = c + (uint32_t)r;
         const int64_t d = (int64_t)k + (int64_t)(t >= w.d ? t - w.d : t) - (int64_t)c;
@@ -219,9 +221,6 @@ extern "C" int lqcd_split_rotate(void *out, const void *in, int64_t nvec, int vl
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     hipStream_t st = (hipStream_t)stream;
     const bool in_wave = 64 % vl == 0;
-    // (off + k < 2^31 + 1024 would leave the 31 bits of fdiv only for vectors
-    // of more than 2^31 - 1024 elements)
-    if (!in_wave && vl > 0x7fffffff - ROT_BLOCK * ROT_PER) return LQCD_EINVAL;
     const dim3 gather((unsigned)((n + ROT_BLOCK * ROT_PER - 1) / (ROT_BLOCK * ROT_PER)));
     const FastDiv dv = make_fastdiv((uint32_t)vl), dw = make_fastdiv((uint32_t)w);
     if (elem_bytes == 8) {

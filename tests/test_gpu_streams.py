@@ -60,3 +60,27 @@ def test_split_rotate_across_blocks(vl, s, nvec, dtype):
         P.split_rotate(out, dev(x), s, r)
         want = np.roll(x.reshape(nvec, s, w), -r, axis=2).reshape(nvec, vl)
         assert np.array_equal(host(out), want), r
+
+
+def test_sums_are_refused_under_capture():
+    """A result for the host cannot come from a stream that is captured: the
+    call returns an error, as a copy does, and the process goes on."""
+    lat = P.Lattice((4, 4, 4, 4))
+    f = P.new_spinor(lat, P.F64, P.EVEN)
+    assert P.norm2(f) == 0.0
+    stream = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    refused = False
+    with torch.cuda.stream(stream):
+        g.capture_begin(capture_error_mode="thread_local")
+        try:
+            P.norm2(f)
+        except P.LQCDError:
+            refused = True
+        try:
+            g.capture_end()
+        except RuntimeError:
+            pass  # the refused call has ended the capture
+    assert refused
+    torch.cuda.synchronize()
+    assert P.norm2(f) == 0.0
