@@ -88,8 +88,8 @@ constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #ifndef LQCD_HOP_TMARCH_MIN_LOG2
 #define LQCD_HOP_TMARCH_MIN_LOG2 17
 #endif
-// Whole-lattice even-odd launches with odd output walk every XCD's range of
-// tiles backwards.  Operators alternate output parities (Mhat, its adjoint,
+// Whole-lattice even-odd launches with odd output (V/2 >= 2^17) walk every
+// XCD's range of tiles backwards.  Operators alternate output parities (Mhat, its adjoint,
 // the solver's four hops), and a hop that starts where the one before it
 // ended finds the last links and spinors of that one in the Infinity Cache;
 // walked the same way round, a working set beyond 256 MB has evicted what the
@@ -288,6 +288,13 @@ static_assert(offsetof(HopArgs, bpp) / 64 == 0 &&
 // tile).  A launch over both parities gives consecutive blocks the even and
 // the odd tile of one region: each reads the links and spinors of the other,
 // so both are fetched into the same XCD's L2 once.
+// BIG (V/2 >= 2^BIG_MIN_LOG2): the launch may walk backwards or in slab order.
+// On smaller lattices, whose launches are as long as the chain from the
+// arguments to the first load, the few scalar instructions of either cost
+// 0.07 us of 3.95 (16^4 FP32-12; 0.1-0.2 of 3.73 binary16), so their kernels
+// are instances of their own.
+constexpr int BIG_MIN_LOG2 = LQCD_BRICK_MIN_LOG2;
+template <bool BIG>
 __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, int &p, int64_t &blk) {
     // selects, not branches: every launch argument is read up front
 #if LQCD_HOP_ARGS_TOUCH
@@ -297,23 +304,24 @@ __device__ __forceinline__ int64_t hop_site_index(const HopArgs &a, int lane, in
     asm volatile("" ::"s"(a.bpp), "s"(a.g.lxh), "s"(a.g.vh), "s"(a.in[0]), "s"(a.stream));
 #endif
     const uint32_t bx = blockIdx.x;
-    blk = LQCD_HOP_XCD ? xcd_block(bx, a.nblk, a.rev) : (int64_t)bx;
+    blk = LQCD_HOP_XCD ? xcd_block(bx, a.nblk, BIG ? a.rev : 0) : (int64_t)bx;
     // paired: blocks 2i / 2i + 1 take the even / odd tile i; otherwise the
     // first bpp blocks take parity par0 and the rest the other parity
     const int q = blk >= a.bpp ? 1 : 0;
     const uint32_t lb = (uint32_t)(a.paired ? blk >> 1 : blk - q * a.bpp);
     p = a.paired ? (int)(blk & 1) : a.par0 ^ q;
-    const int64_t tile = brick_tile(a, lb);
+    const int64_t tile = brick_order<BIG>(lb, a.brick, a.g);
     // the partial of a tile in slab order, whose blocks outnumber the tiles,
     // goes by the tile
-    if (a.brick.lz == 0) blk = tile;
+    if (BIG && a.brick.lz == 0) blk = tile;
     return tile * HOP_SITES + lane;
 }
 
 // 4-way shape: wave w computes both hops of direction w; waves 1..3 leave
 // their partial spinors in LDS and wave 0 adds them up.  CT: real type of a
 // canonical output, void for the internal layout.
-template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO, typename CT = void, int CG = CG_NONE>
+template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO, typename CT = void, int CG = CG_NONE,
+          bool BIG = true>
 __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
     __shared__ alignas(16) cplx<T> part[3][12][64];
@@ -321,7 +329,7 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     const int w = threadIdx.x >> 6;
     int p;
     int64_t blk;
-    const int64_t s = hop_site_index(a, lane, p, blk);
+    const int64_t s = hop_site_index<BIG>(a, lane, p, blk);
     const Geom &g = a.g;
     const bool active = s < g.vh;
     // (coordinates of a padding site are never used, and s < 2^31 anyway;
@@ -525,7 +533,7 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
     const int lane = threadIdx.x & 63;
     int p;
     int64_t blk;
-    const int64_t s = hop_site_index(a, lane, p, blk);
+    const int64_t s = hop_site_index<true>(a, lane, p, blk);
     const Geom &g = a.g;
     const bool active = s < g.vh;
     const Coord c = cb_coords(g, p, s);
@@ -618,7 +626,7 @@ __device__ __forceinline__ void rebuild_row(const HopArgs &a, int p, int64_t s,
 // stages the two colour vectors of its multiplied half-spinor in LDS; wave 0
 // rebuilds the four spin rows from the eight staged half-spinors.
 template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool ROWS, bool HALO, typename CT = void,
-          int CG = CG_NONE>
+          int CG = CG_NONE, bool BIG = true>
 __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     using T = typename real_of<P>::type;
     __shared__ alignas(16) cplx<T> chi[8][6][64];
@@ -626,7 +634,7 @@ __global__ __launch_bounds__(512) void hop8_kernel(HopArgs a) {
     const int w = threadIdx.x >> 6;
     int p;
     int64_t blk;
-    const int64_t s = hop_site_index(a, lane, p, blk);
+    const int64_t s = hop_site_index<BIG>(a, lane, p, blk);
     const Geom &g = a.g;
     const bool active = s < g.vh;
     // (as in the 4-way shape)
@@ -726,7 +734,8 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
         if (a.cg >= CG_RESID) {
 #define LQCD_RESID(PI)                                                                             \
     if (a.cg == CG_RESID + PI) {                                                                   \
-        hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI><<<grid, 256, a.lds_extra, st>>>(a); \
+        if (NTM < 2 && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI, (NTM >= 2)><<<grid, 256, a.lds_extra, st>>>(a); \
+        else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI, true><<<grid, 256, a.lds_extra, st>>>(a); \
         return;                                                                                    \
     }
             LQCD_RESID(LQCD_F64)
@@ -739,15 +748,15 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
     if constexpr (P != LQCD_F16 && !DAG && !HALO && NTM < 2 && (HASY ? NORM == 1 : NORM == 0)) {
         constexpr int role = HASY ? CG_DIR_Y : CG_DIR_IN;
         if (a.cg == role) {
-            if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role><<<grid, 512, 0, st>>>(a);
-            else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, role><<<grid, 256, 0, st>>>(a);
+            if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role, false><<<grid, 512, 0, st>>>(a);
+            else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, role, false><<<grid, 256, 0, st>>>(a);
             return;
         }
     }
     if constexpr (DAG && !HASY && !NORM && !HALO) {
         if (a.cg == CG_PRE) {
             if constexpr (hop_shape(P) == 8) {
-                if (a.rows) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
+                if (a.rows) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_PRE, false><<<grid, 512, 0, st>>>(a);
                 else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
             } else {
                 hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_PRE><<<grid, 256, a.lds_extra, st>>>(a);
@@ -760,11 +769,13 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
     } else if constexpr (hop_shape(P) == 8) {
         if constexpr (P == LQCD_F32 && !HASY && !NORM) {
             if (a.rows) {
-                hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO><<<grid, 512, 0, st>>>(a);
+                hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_NONE, false><<<grid, 512, 0, st>>>(a);
                 return;
             }
         }
-        hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO><<<grid, 512, 0, st>>>(a);
+        constexpr bool big = NTM >= 2;  // links beyond the caches
+        if (!big && a.small) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, big><<<grid, 512, 0, st>>>(a);
+        else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, !HALO><<<grid, 512, 0, st>>>(a);
     } else {
         if constexpr (!HALO && LQCD_HOP_TMARCH > 0) {
             if (a.tseg > 0) {
@@ -772,7 +783,9 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
                 return;
             }
         }
-        hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO><<<grid, 256, a.lds_extra, st>>>(a);
+        constexpr bool big = NTM >= 2;
+        if (!big && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, big><<<grid, 256, a.lds_extra, st>>>(a);
+        else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, !HALO><<<grid, 256, a.lds_extra, st>>>(a);
     }
 }
 
@@ -894,7 +907,8 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
         const bool two = a.paired && link == 18 && (plain || wide);
         a.lds_extra = two ? F64_LDS_TWO : F64_LDS_THREE;
     }
-    a.rev = LQCD_HOP_ZIGZAG && nparity == 1 && region < 0 && a.par0 == LQCD_ODD;
+    a.small = a.g.vh < ((int64_t)1 << BIG_MIN_LOG2) || region >= 0;
+    a.rev = LQCD_HOP_ZIGZAG && nparity == 1 && !a.small && a.par0 == LQCD_ODD;
     dim3 grid((unsigned)(a.bpp * nparity));
     // t-march launches (4-way shape, one parity, whole lattice, whole tiles
     // per t-slice in a multiple of 8 columns): one block per column and

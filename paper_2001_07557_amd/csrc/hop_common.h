@@ -118,7 +118,8 @@ __device__ __forceinline__ void hop_fence(cplx<T> acc[N]) {
 // 46^3x50 FP64-18 1379 -> 1159, 18^2x42x40 FP64-12 121.1 -> 116.  Slabs half
 // as thick, two per XCD, lose 5-8% (the planes at every edge are read again).
 __host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t, uint32_t j) {
-    return (t * (uint32_t)g.st + (uint32_t)(j * g.st >> 3) + (TILE - 1)) >> TILE_SHIFT;
+    const uint32_t st = (uint32_t)g.st;
+    return (t * st + j * (st >> 3) + (j * (st & 7) >> 3) + (TILE - 1)) >> TILE_SHIFT;
 }
 
 // Launches of the solver.  CG_UPDATE: the adjoint hop that completes A p and
@@ -181,6 +182,7 @@ struct HopArgs {
     int par0;             // parity of the first bpp blocks
     int paired;           // both parities: block 2i / 2i + 1 = even / odd tile i
     uint32_t nblk;        // blocks in the grid
+    int rev;              // walk each XCD's range of tiles backwards (BIG launches)
     Brick brick;          // cache-blocked tile order (identity: plain order)
     Geom g;
     char *out[2];         // output half field for output parity p
@@ -190,7 +192,6 @@ struct HopArgs {
     double alpha, beta;
     double *partial;      // optional per-block |out|^2
     int stream;           // non-temporal hints: bit 0 output stores, bit 1 link loads
-    int rev;              // walk each XCD's range of tiles backwards
     int rows;             // 8-way shape: waves 0-3 rebuild one spin row each
     // boundary-slice launches: the t-hops that cross the t boundary read
     // face[0] (projected half-spinors of the forward neighbours) and face[1]
@@ -215,6 +216,8 @@ struct HopArgs {
     uint32_t lds_extra;
     // t-march launches: t-slices per block (0: one tile per block)
     int tseg;
+    // host side: kernels without the large lattices' orders (BIG false)
+    int small;
     // host side: out[0] is a canonical array of reals of this many bytes (8
     // or 4; both-parity launches, FP64 and FP32 storage); 0: internal layout
     int canon;
@@ -225,6 +228,8 @@ struct HopArgs {
 // the three t-slices of a brick that one output slice touches stay in the
 // XCD's L2, where the plain order would revisit each input slice from memory
 // for the t-neighbours of the slices before and after it.
+// SLABS: the slab order may be asked for.
+template <bool SLABS = true>
 __host__ __device__ __forceinline__ int64_t brick_order(uint32_t b, const Brick &k, const Geom &g) {
     const uint32_t r1 = fdiv(b, k.pt);    // (z-group, t) in traversal order
     const uint32_t r2 = fdiv(r1, k.bz);   // (brick, band, t)
@@ -234,16 +239,14 @@ __host__ __device__ __forceinline__ int64_t brick_order(uint32_t b, const Brick 
     const uint32_t zi = r1 - r2 * k.bz.d;
     const uint32_t t = k.t0 + (r2 - r3 * k.lt.d) * k.tstep;
     const uint32_t band = r3 - zc * k.nyb.d;
-    if (k.lz == 0) {
-        // (bz = nyb = 1: zc is the slab)
-        const uint32_t at = slab_tile(g, t, zc) + tile;
-        return at < slab_tile(g, t, zc + 1) ? (int64_t)at : g.ntiles;
+    if constexpr (SLABS) {
+        // both orders, then a select: a branch would put the argument loads
+        // behind it one after the other
+        const uint32_t at = slab_tile(g, t, zc) + tile;  // (bz = nyb = 1: zc is the slab)
+        const uint32_t slab = at < slab_tile(g, t, zc + 1) ? at : (uint32_t)g.ntiles;
+        if (k.lz == 0) return (int64_t)slab;
     }
     return (int64_t)((t * k.lz + zc * k.bz.d + zi) * k.ptg + band * k.pt.d + tile);
-}
-
-__device__ __forceinline__ int64_t brick_tile(const HopArgs &a, uint32_t b) {
-    return brick_order(b, a.brick, a.g);
 }
 
 // Blocked traversal plan: the tiles of a z-group (the fewest consecutive
