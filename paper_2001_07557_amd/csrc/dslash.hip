@@ -773,8 +773,7 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
                 return;
             }
         }
-        constexpr bool big = NTM >= 2;  // links beyond the caches
-        if (!big && a.small) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, big><<<grid, 512, 0, st>>>(a);
+        if (a.small) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, false><<<grid, 512, 0, st>>>(a);
         else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, !HALO><<<grid, 512, 0, st>>>(a);
     } else {
         if constexpr (!HALO && LQCD_HOP_TMARCH > 0) {
@@ -783,8 +782,7 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
                 return;
             }
         }
-        constexpr bool big = NTM >= 2;
-        if (!big && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, big><<<grid, 256, a.lds_extra, st>>>(a);
+        if (a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, false><<<grid, 256, a.lds_extra, st>>>(a);
         else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, !HALO><<<grid, 256, a.lds_extra, st>>>(a);
     }
 }
