@@ -74,6 +74,11 @@ constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #ifndef LQCD_HOP_F64_LDS_MIN_LOG2
 #define LQCD_HOP_F64_LDS_MIN_LOG2 17
 #endif
+// (t-region launches, short as they are, only from 2^20: 32^3x8 FP64-18 face
+// pack, interior and boundary 49.6 us with three blocks, 48.9 with four)
+#ifndef LQCD_HOP_F64_REGION_LDS_MIN_LOG2
+#define LQCD_HOP_F64_REGION_LDS_MIN_LOG2 20
+#endif
 #ifndef LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2
 #define LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2 15
 #endif
@@ -373,8 +378,9 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     constexpr bool early = early_y<P, NORM, NTM>();
     if (early && w == 0 && active) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
     __syncthreads();
-    // (FP64: before the LDS sums, M 32^4 FP64-12 193.4 -> 191.3 us)
-    constexpr bool first_y = P == LQCD_F64 && CG != CG_DIR_Y;
+    // (FP64 on large lattices: before the LDS sums, M 32^4 FP64-12 193.4 -> 191.3
+    // us; on small ones after them, Mhat 20^3x18 FP64-18 47.7 -> 47.3)
+    constexpr bool first_y = P == LQCD_F64 && CG != CG_DIR_Y && BIG;
     double nrm[2] = {0.0, 0.0};
     if (w == 0 && active) {
         if (!early && first_y) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
@@ -899,7 +905,9 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     a.stream = LQCD_HOP_STREAM >= 0 ? LQCD_HOP_STREAM : (out_nt ? 1 : 0) | (link_nt ? 2 : 0);
     a.lds_extra = LQCD_HOP_EXTRA_LDS >= 0 ? (uint32_t)LQCD_HOP_EXTRA_LDS : 0u;
     if (LQCD_HOP_EXTRA_LDS < 0 && prec == LQCD_F64 &&
-        a.g.vh >= ((int64_t)1 << (a.paired ? LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2 : LQCD_HOP_F64_LDS_MIN_LOG2))) {
+        a.g.vh >= ((int64_t)1 << (a.paired      ? LQCD_HOP_F64_PAIRED_LDS_MIN_LOG2
+                                  : region < 0 ? LQCD_HOP_F64_LDS_MIN_LOG2
+                                               : LQCD_HOP_F64_REGION_LDS_MIN_LOG2))) {
         const bool plain = a.brick.lz == 1 && a.g.vh >= ((int64_t)1 << LQCD_BRICK_MIN_LOG2);
         const bool wide = a.brick.lz == 0 && a.g.st * (2 * 3 * 192 / 8) > F64_SLAB_TWO_BYTES;
         const bool two = a.paired && link == 18 && (plain || wide);
