@@ -379,7 +379,8 @@ __global__ __launch_bounds__(256) void hop4_kernel(HopArgs a) {
     if (early && w == 0 && active) load_y<P, HASY, CG == CG_DIR_Y>(a, p, s, y);
     __syncthreads();
     // (FP64 on large lattices: before the LDS sums, M 32^4 FP64-12 193.4 -> 191.3
-    // us; on small ones after them, Mhat 20^3x18 FP64-18 47.7 -> 47.3)
+    // us; on small ones after them, where neither order was measurably faster:
+    // Mhat 20^3x18 FP64-18 47.7 to 47.9)
     constexpr bool first_y = P == LQCD_F64 && CG != CG_DIR_Y && BIG;
     double nrm[2] = {0.0, 0.0};
     if (w == 0 && active) {
