@@ -6,7 +6,10 @@
 //
 // One 4 KiB page per process, allocated at the first use and kept (64 slots,
 // each given out to one call at a time and handed back at its end); a call
-// that finds no slot, or no page, copies as before.
+// that finds no slot, or no page, copies as before.  The next owner of a slot
+// numbers its posts on from the slot's count, so a slot is handed back only
+// when every post numbered so far has landed: a call that gives up after a
+// launch drains its stream first, and where that fails the slot is retired.
 #pragma once
 
 #include "lqcd_internal.h"
@@ -38,6 +41,7 @@ private:
     Mail *m_ = nullptr;
     uint64_t n_ = 0;
     int slot_ = -1;
+    hipStream_t st_ = nullptr;
 };
 
 // One thread of the grid posts v[0..1].

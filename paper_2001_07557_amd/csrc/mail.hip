@@ -38,6 +38,7 @@ void MailSlot::open(hipStream_t st) {
         if (!((mail_used >> i) & 1)) {
             mail_used |= (uint64_t)1 << i;
             slot_ = i;
+            st_ = st;
             m_ = mail_page + i;
             n_ = __atomic_load_n(&m_->count, __ATOMIC_ACQUIRE);
             return;
@@ -46,6 +47,13 @@ void MailSlot::open(hipStream_t st) {
 
 MailSlot::~MailSlot() {
     if (slot_ < 0) return;
+    // a post that is still to come would carry the number of the next owner's
+    // first (a launch that failed never posts: its number is not reached, and
+    // nothing is pending once the stream has drained)
+    if (__atomic_load_n(&m_->count, __ATOMIC_ACQUIRE) != n_ && hipStreamSynchronize(st_) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
     std::lock_guard<std::mutex> lock(mail_mutex);
     mail_used &= ~((uint64_t)1 << slot_);
 }

@@ -1,0 +1,135 @@
+// Host check of the slots through which kernels post numbers (csrc/mail.hip),
+// with the few HIP calls it makes replaced by a stream that is played by hand:
+// posts are queued and land when the stream is drained, or when told to.
+// Prints one line per check and "checks N bad B".
+#include <string.h>
+
+#include "mail.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <ctime>
+#include <deque>
+
+namespace {
+
+struct Post {
+    lqcd::Mail *m;
+    uint64_t count;
+    double v[2];
+};
+std::deque<Post> queue;   // enqueued, not yet run
+bool drain_fails = false;
+int drains = 0;
+
+void enqueue(lqcd::MailSlot &s, double a, double b) { queue.push_back({s.get(), s.next(), {a, b}}); }
+void run_all() {
+    for (; !queue.empty(); queue.pop_front()) {
+        const Post &p = queue.front();
+        p.m->v[0] = p.v[0];
+        p.m->v[1] = p.v[1];
+        __atomic_store_n(&p.m->count, p.count, __ATOMIC_RELEASE);
+    }
+}
+
+int checks = 0, bad = 0;
+void check(bool ok, const char *what) {
+    ++checks;
+    bad += !ok;
+    printf("%s %s\n", ok ? "ok  " : "FAIL", what);
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+    *s = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    *p = aligned_alloc(4096, n);
+    ::memset(*p, 0, n);
+    return hipSuccess;
+}
+hipError_t hipStreamQuery(hipStream_t) {
+    if (drain_fails) return hipErrorUnknown;
+    return queue.empty() ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+    ++drains;
+    if (drain_fails) return hipErrorUnknown;
+    run_all();
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+}
+
+namespace lqcd {
+void set_hip_error(hipError_t) {}
+}
+
+using namespace lqcd;
+
+int main() {
+    setvbuf(stdout, nullptr, _IONBF, 0);
+    // a call that gives up after its launch: the next one must not take its number
+    {
+        Mail *first;
+        {
+            MailSlot a;
+            a.open(nullptr);
+            first = a.get();
+            enqueue(a, 1.0, -1.0);
+        }
+        check(queue.empty() || drains > 0, "an abandoned post is waited for");
+        MailSlot b;
+        b.open(nullptr);
+        const uint64_t before = __atomic_load_n(&b.get()->count, __ATOMIC_ACQUIRE);
+        const uint64_t n = b.next();
+        run_all();
+        check(b.get() != first || __atomic_load_n(&first->count, __ATOMIC_ACQUIRE) != n,
+              "a late post does not carry the next owner's number");
+        check(b.get()->count == before, "no post lands in the slot of another call");
+    }
+    // the same where the stream cannot be drained: the slot is never given out again
+    {
+        Mail *lost;
+        {
+            MailSlot a;
+            a.open(nullptr);
+            lost = a.get();
+            enqueue(a, 2.0, -2.0);
+            drain_fails = true;
+        }
+        drain_fails = false;
+        MailSlot b;
+        b.open(nullptr);
+        check(b.get() && b.get() != lost, "a slot whose post may still come is retired");
+        run_all();
+    }
+    // slots run out, come back, and the numbers of a slot go on
+    {
+        MailSlot many[80];
+        int got = 0;
+        for (auto &s : many) {
+            s.open(nullptr);
+            got += s.get() != nullptr;
+        }
+        check(got < 80 && got >= 60, "a call that finds no slot gets none");
+    }
+    {
+        MailSlot a;
+        a.open(nullptr);
+        double out[2];
+        bool ok = a.get() != nullptr;
+        for (int i = 0; i < 5 && ok; ++i) {
+            enqueue(a, i, i + 0.5);
+            run_all();
+            ok = a.wait(nullptr, out, 2) == LQCD_OK && out[0] == i && out[1] == i + 0.5;
+        }
+        check(ok, "posts of one call arrive in order");
+    }
+    printf("checks %d bad %d\n", checks, bad);
+    return bad ? 1 : 0;
+}
