@@ -241,9 +241,10 @@ int lqcd_mhat(const lqcd_geom_t *g, void *out_e, const void *in_e, void *tmp_o,
 size_t lqcd_reduce_workspace_bytes(const lqcd_geom_t *g, int subset);
 
 /* result[0] + i result[1] = <a, b> = sum conj(a) b over every site of the
-   subset (host array of 2 doubles).  Per-thread partials in the field's
-   arithmetic precision, wave64 and block sums in FP64, final sum over blocks
-   in a fixed order: bitwise reproducible.  Synchronises the stream. */
+   subset (host array of 2 doubles).  Sums of one 16-byte word's products
+   (binary16: of one site's) in the field's arithmetic precision, everything
+   above in FP64, the blocks added in a fixed order: bitwise reproducible.
+   Synchronises the stream. */
 int lqcd_dot(const lqcd_geom_t *g, int subset, const void *a, const void *b, int prec,
              void *workspace, double *result, void *stream);
 

@@ -1,7 +1,9 @@
 // BLAS-1 on internal spinor fields: inner products and norms with
-// deterministic wave64 -> block -> grid reductions (FP64 from the block level
-// up), y = a x + b y, and precision conversion.  One thread per site; a
-// FULL field is the even half followed by the odd half.
+// deterministic wave64 -> block -> grid reductions, y = a x + b y, and
+// precision conversion.  FP64 and FP32 fields are reduced and updated as runs of
+// 16-byte words (the sum of a word's products in the field's arithmetic, all
+// above it in FP64), binary16 fields and conversions site by site; a FULL
+// field is the even half followed by the odd half.
 
 #include <mutex>
 
@@ -60,9 +62,9 @@ __device__ __forceinline__ void reduce_word(v4u wa, v4u wb, double acc[2]) {
 // the words of one tile); lanes past the last site of a half are left out.
 // binary16 fields are read site by site, for the scale.  Whole call at 32^4,
 // full field (us, before -> now, the posted result and the shorter final sum
-// included): <a, b> FP64 99 -> 85, FP32 67 -> 52, |a|^2 FP64 66 -> 52, FP32 49
-// -> 33; at 8^4 31.6 -> 17.  Four or eight words in flight, or 1024 or 4096
-// blocks: 91-100 us for the first.
+// included): <a, b> FP64 98 -> 86, FP32 60.6 -> 49, |a|^2 FP64 61 -> 51, FP32 47
+// -> 36; at 8^4 31.5 -> 21.  Four or eight words in flight, or 1024 or 4096
+// blocks: 6-15 us more for the first.
 template <int P, bool DOT, bool RAGGED>
 __global__ __launch_bounds__(RED_BLOCK) void reduce_k(const char *a, const char *b, int64_t vh,
                                                       int64_t ntiles, int nhalf, int64_t hb, double *partial) {
@@ -300,18 +302,18 @@ static int reduce_entry(const lqcd_geom_t *gg, int subset, const void *a, const 
 #endif
     int rc = check_launch();
     if (rc) return rc;
+    // the stream is synchronised, as the interface says, whichever way the
+    // result comes; a posted one saves the copy (|a|^2 at 4^4, whole call: 31
+    // -> 20 us; 14 without the synchronisation)
     double host[2];
-    if (mail.get()) {
-        rc = mail.wait(st, host, 2);
-        if (rc) return rc;
-    } else {
-        hipError_t e = hipMemcpyAsync(host, out, sizeof(host), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) {
-            set_hip_error(e);
-            return LQCD_EHIP;
-        }
+    hipError_t e = hipSuccess;
+    if (!mail.get()) e = hipMemcpyAsync(host, out, sizeof(host), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        set_hip_error(e);
+        return LQCD_EHIP;
     }
+    if (mail.get() && (rc = mail.take(host, 2)) != LQCD_OK) return rc;
     result[0] = host[0];
     if (b) result[1] = host[1];
     return LQCD_OK;

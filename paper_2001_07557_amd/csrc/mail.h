@@ -36,6 +36,8 @@ public:
     uint64_t next() { return ++n_; }
     // waits for the post numbered last by next(), made by a kernel on st
     int wait(hipStream_t st, double *out, int nv);
+    // the post numbered last, its stream having been synchronised
+    int take(double *out, int nv) const;
 
 private:
     Mail *m_ = nullptr;

@@ -76,6 +76,14 @@ int MailSlot::wait(hipStream_t st, double *out, int nv) {
             }
         }
     }
+    return take(out, nv);
+}
+
+int MailSlot::take(double *out, int nv) const {
+    if (__atomic_load_n(&m_->count, __ATOMIC_ACQUIRE) != n_) {
+        set_hip_error(hipErrorUnknown);
+        return LQCD_EHIP;
+    }
     for (int i = 0; i < nv; ++i) __atomic_load(&m_->v[i], &out[i], __ATOMIC_RELAXED);
     return LQCD_OK;
 }

@@ -42,3 +42,20 @@ def test_sum_after_a_call_that_gave_up():
     torch.cuda.synchronize()
     assert first == -2 and second == 0
     assert res[1][0] == 9.0 * 24.0 * lat.volume
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 16)])
+@pytest.mark.parametrize("busy", [0, 1_000_000])
+def test_sums_synchronise_the_stream(dims, busy):
+    """lqcd_dot and lqcd_norm2 return when the stream has drained."""
+    lat = P.Lattice(dims)
+    f = field(lat, 1.0)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        for call in (lambda: P.norm2(f), lambda: P.dot(f, f).real):
+            for _ in range(20):
+                if busy:
+                    torch.cuda._sleep(busy)
+                assert call() == 24.0 * lat.volume
+                assert stream.query()
