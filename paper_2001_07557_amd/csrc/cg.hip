@@ -400,7 +400,7 @@ struct Solver {
                                                  mail.get() ? mail.next() : 0);
         const int rc = check_launch();
         if (rc) return rc;
-        if (mail.get()) return mail.wait(st, host, nv);
+        if (mail.get()) return mail.wait(host, nv);
         hipError_t e = hipMemcpyAsync(host, w.sc + CG_OUT, nv * sizeof(double), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {

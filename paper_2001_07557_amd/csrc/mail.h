@@ -34,9 +34,10 @@ public:
     Mail *get() const { return m_; }
     // the number of the next post
     uint64_t next() { return ++n_; }
-    // waits for the post numbered last by next(), made by a kernel on st
-    int wait(hipStream_t st, double *out, int nv);
-    // the post numbered last, its stream having been synchronised
+    // waits for the post numbered last by next(), made by a kernel on the
+    // slot's stream: watched for some milliseconds, then by synchronising
+    int wait(double *out, int nv);
+    // the post numbered last, the stream having been synchronised
     int take(double *out, int nv) const;
 
 private:

@@ -52,10 +52,6 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
     ::memset(*p, 0, n);
     return hipSuccess;
 }
-hipError_t hipStreamQuery(hipStream_t) {
-    if (drain_fails) return hipErrorUnknown;
-    return queue.empty() ? hipSuccess : hipErrorNotReady;
-}
 hipError_t hipStreamSynchronize(hipStream_t) {
     ++drains;
     if (drain_fails) return hipErrorUnknown;
@@ -108,6 +104,35 @@ int main() {
         check(b.get() && b.get() != lost, "a slot whose post may still come is retired");
         run_all();
     }
+    // a post that does not come while the host watches: it stops watching and
+    // lets the runtime wait
+    {
+        MailSlot a;
+        a.open(nullptr);
+        enqueue(a, 3.0, 4.0);
+        double out[2] = {0, 0};
+        const int was = drains;
+        const clock_t t0 = clock();
+        const int rc = a.wait(out, 2);
+        const double cpu = (double)(clock() - t0) / CLOCKS_PER_SEC;
+        check(rc == LQCD_OK && out[0] == 3.0 && out[1] == 4.0, "a late post is received");
+        check(drains > was && cpu < 1.0, "the host stops watching after a while");
+    }
+    // a stream that fails, and one that ends without a post
+    {
+        MailSlot a;
+        a.open(nullptr);
+        enqueue(a, 5.0, 6.0);
+        drain_fails = true;
+        double out[2];
+        check(a.wait(out, 2) == LQCD_EHIP, "a stream error is returned");
+        drain_fails = false;
+        run_all();
+        MailSlot b;
+        b.open(nullptr);
+        b.next();
+        check(b.wait(out, 2) == LQCD_EHIP, "a post that never comes is an error");
+    }
     // slots run out, come back, and the numbers of a slot go on
     {
         MailSlot many[80];
@@ -126,7 +151,7 @@ int main() {
         for (int i = 0; i < 5 && ok; ++i) {
             enqueue(a, i, i + 0.5);
             run_all();
-            ok = a.wait(nullptr, out, 2) == LQCD_OK && out[0] == i && out[1] == i + 0.5;
+            ok = a.wait(out, 2) == LQCD_OK && out[0] == i && out[1] == i + 0.5;
         }
         check(ok, "posts of one call arrive in order");
     }

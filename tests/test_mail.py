@@ -23,4 +23,4 @@ def test_slots_are_given_out_again_only_when_their_posts_have_landed(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
     last = r.stdout.strip().splitlines()[-1].split()
-    assert last[0] == "checks" and int(last[1]) >= 6 and last[2:] == ["bad", "0"], r.stdout
+    assert last[0] == "checks" and int(last[1]) >= 9 and last[2:] == ["bad", "0"], r.stdout
