@@ -155,12 +155,23 @@ __global__ __launch_bounds__(FIN_BLOCK) void finalize_k(const double *partial, i
     }
 }
 
+// Kernels of one 16-byte word per thread.  A launch counts its work items in
+// 32 bits per dimension and drops what is beyond (an FP64 full field of V >=
+// 357.9M sites, 69 GB, has more words), so the blocks beyond 2^23 go into y.
+static dim3 word_grid(int64_t n) {
+    const int64_t blocks = (n + RED_BLOCK - 1) / RED_BLOCK, row = (int64_t)1 << 23;
+    return dim3((unsigned)(blocks < row ? blocks : row), (unsigned)((blocks + row - 1) / row));
+}
+__device__ __forceinline__ int64_t word_index() {
+    return ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * RED_BLOCK + threadIdx.x;
+}
+
 // y = a x + b y on 16-byte words (FP64, FP32): one word per thread, as the
 // copy below (a thread per site: 118 us at 32^4 FP64, full field; now 105, 5.7
 // TB/s; FP32 57.4 -> 53.8).
 template <typename T>
 __global__ __launch_bounds__(RED_BLOCK) void axpby_words_k(T a, const v4u *x, T b, v4u *y, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * RED_BLOCK + threadIdx.x;
+    const int64_t i = word_index();
     if (i >= n) return;
     constexpr int R = WORD / (int)sizeof(T);
     T vx[R], vy[R];
@@ -398,7 +409,7 @@ extern "C" int lqcd_axpby(const lqcd_geom_t *gg, int subset, double a, const voi
     if (!al16(x) || !al16(y)) return LQCD_EINVAL;
     const int64_t hb = (int64_t)half_spinor_bytes(g, prec);
     const int64_t n = prec == LQCD_F16 ? g.vh * nh : hb * nh / WORD;
-    dim3 grid((unsigned)((n + RED_BLOCK - 1) / RED_BLOCK)), block(RED_BLOCK);
+    const dim3 grid = word_grid(n), block(RED_BLOCK);
     hipStream_t st = (hipStream_t)stream;
     if (prec == LQCD_F64) axpby_words_k<double><<<grid, block, 0, st>>>(a, (const v4u *)x, b, (v4u *)y, n);
     else if (prec == LQCD_F32) axpby_words_k<float><<<grid, block, 0, st>>>((float)a, (const v4u *)x, (float)b, (v4u *)y, n);

@@ -1,0 +1,26 @@
+"""Fields of more 16-byte words than one dimension of a launch can count work
+items (2^32): accepted by every kernel that walks a field word by word."""
+
+import pytest
+import torch
+
+import paper_2001_07557_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+def test_axpby_beyond_2_to_32_words():
+    lat = P.Lattice((128, 128, 148, 148))
+    n = lat.spinor_bytes(P.F64, P.FULL)
+    assert n // 16 > 1 << 32
+    torch.cuda.empty_cache()
+    y = P.new_spinor(lat, P.F64, P.FULL, zero=False)
+    v = y.buf[:n].view(torch.float64)
+    v.fill_(2.0)
+    P.axpby(0.5, y, 0.25, y)  # each word is read before it is written
+    step = 1 << 28
+    for at in range(0, v.numel(), step):
+        right = torch.all(v[at:at + step] == 1.5).item()
+        assert right, at
+    del v, y
+    torch.cuda.empty_cache()
