@@ -221,7 +221,7 @@ __global__ __launch_bounds__(RED_BLOCK) void convert_k(char *dst, const char *sr
 // 16-byte word per thread (a thread per site moving all its words measured
 // 5.3 TB/s on a 4 GB copy against 6.2 TB/s for one word per thread).
 __global__ __launch_bounds__(RED_BLOCK) void copy_words_k(v4u *dst, const v4u *src, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = word_index();
     if (i < n) dst[i] = src[i];
 }
 
@@ -229,8 +229,7 @@ void launch_convert(const Geom &g, int nhalf, char *dst, int pd, const char *src
                     hipStream_t st) {
     if (pd == ps) {
         const int64_t words = (int64_t)half_spinor_bytes(g, pd) * nhalf / 16;
-        dim3 grid((unsigned)((words + RED_BLOCK - 1) / RED_BLOCK)), block(RED_BLOCK);
-        copy_words_k<<<grid, block, 0, st>>>((v4u *)dst, (const v4u *)src, words);
+        copy_words_k<<<word_grid(words), RED_BLOCK, 0, st>>>((v4u *)dst, (const v4u *)src, words);
         return;
     }
     const int64_t n = g.vh * nhalf;

@@ -24,3 +24,21 @@ def test_axpby_beyond_2_to_32_words():
         assert right, at
     del v, y
     torch.cuda.empty_cache()
+
+
+def test_same_precision_convert_beyond_2_to_32_words():
+    lat = P.Lattice((128, 128, 148, 148))
+    n = lat.spinor_bytes(P.F64, P.FULL)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 2 * n + (8 << 30):
+        pytest.skip("two fields of 69 GB do not fit")
+    src, dst = (P.new_spinor(lat, P.F64, P.FULL, zero=False) for _ in range(2))
+    src.buf[:n].view(torch.float64).fill_(2.0)
+    dst.buf.fill_(0xFF)
+    P.convert(dst, src)
+    v, step = dst.buf[:n].view(torch.float64), 1 << 28
+    for at in range(0, v.numel(), step):
+        right = torch.all(v[at:at + step] == 2.0).item()
+        assert right, at
+    del v, src, dst
+    torch.cuda.empty_cache()
