@@ -929,6 +929,8 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
         grid = dim3((unsigned)((a.g.st / TILE) * nseg));
         a.lds_extra = LQCD_HOP_EXTRA_LDS >= 0 ? (uint32_t)LQCD_HOP_EXTRA_LDS : 0u;
     }
+    // a launch counts its work items in 32 bits and drops what is beyond
+    if ((int64_t)grid.x * (hop_shape(prec) == 8 ? 512 : 256) > UINT32_MAX) return LQCD_EINVAL;
     a.nblk = grid.x;
     const bool hasy = a.y[0] != nullptr || a.y[1] != nullptr;
     const int norm = a.cg == CG_UPDATE ? 2 : a.partial != nullptr ? 1 : 0;

@@ -328,6 +328,15 @@ inline Brick make_brick(const Geom &g, const BrickPlan &b) {
     return k;
 }
 
+// Most tiles of a slab in one slice: a run of n sites holds the first sites of
+// at most ceil(n / 64) tiles, and the runs are of floor(st / 8) or ceil(st / 8)
+// sites.  (Attained: the first two runs of a lattice start on a tile wherever
+// the difference matters.  Counting them slab by slab took 8 Lt steps of
+// every launch on the host: 2 us at Lt = 512, 0.28 ms at the longest Lt.)
+inline uint32_t slab_tiles(const Geom &g) {
+    return (uint32_t)(((g.st + 7) / 8 + (TILE - 1)) >> TILE_SHIFT);
+}
+
 // Slab order for lattices that the blocked order does not cover, from V/2 >=
 // 2^LQCD_BRICK_MIN_LOG2 sites as the bricks and where a slab of a slice is at
 // least eight tiles (the pad stays small).  A slab thinner than 1.5 planes
@@ -339,18 +348,12 @@ inline Brick make_brick(const Geom &g, const BrickPlan &b) {
 #ifndef LQCD_HOP_SLABS
 #define LQCD_HOP_SLABS 1
 #endif
+// (a launch counts its work items in 32 bits: where the pads put it beyond
+// them, 82x10^2x65470 in FP32 for one, it keeps the plain order)
 inline bool use_slabs(const Geom &g, const BrickPlan &b, bool both) {
     return LQCD_HOP_SLABS && b.bz == 0 && g.vh >= ((int64_t)1 << LQCD_BRICK_MIN_LOG2) &&
-           g.st >= 8 * 8 * TILE && (both || g.L[2] >= 12);
-}
-
-// Most tiles of a slab in one slice: a run of n sites holds the first sites of
-// at most ceil(n / 64) tiles, and the runs are of floor(st / 8) or ceil(st / 8)
-// sites.  (Attained: the first two runs of a lattice start on a tile wherever
-// the difference matters.  Counting them slab by slab took 8 Lt steps of
-// every launch on the host: 2 us at Lt = 512, 0.28 ms at the longest Lt.)
-inline uint32_t slab_tiles(const Geom &g) {
-    return (uint32_t)(((g.st + 7) / 8 + (TILE - 1)) >> TILE_SHIFT);
+           g.st >= 8 * 8 * TILE && (both || g.L[2] >= 12) &&
+           (int64_t)8 * g.L[3] * slab_tiles(g) * (both ? 2 : 1) * 512 <= UINT32_MAX;
 }
 
 inline Brick make_slab_brick(const Geom &g) {

@@ -1,6 +1,8 @@
 // Host check of the slab order's plan (csrc/hop_common.h): the most tiles of a
 // slab in one slice, which the launch takes from a closed form, against a
-// count over all slabs and slices.  Prints "cases N bad B".
+// count over all slabs and slices; and that the pads of the order never put a
+// launch of 512 threads per block beyond the 2^32 work items that one counts.
+// Prints "cases N bad B".
 #include "lqcd_internal.h"
 #include "hop_common.h"
 
@@ -48,6 +50,20 @@ int main() {
             const int rest = (512 * m + 4) / (2 * y);
             if ((512 * m + 4) % (2 * y) == 0) one(geom(2 * rest, y, 2, 40));
         }
+    for (int t = 1000; t <= 65536; t += t < 60000 ? 1000 : 14)
+        for (int x : {82, 86, 94, 98, 102})
+            for (bool both : {false, true}) {
+                const Geom g = geom(x, 10, 10, t);
+                const int64_t plain = g.ntiles * (both ? 2 : 1) * 512;
+                if (plain > UINT32_MAX) continue;
+                const Brick k = launch_brick(g, LQCD_F32, both ? 2 : 0, both);
+                ++cases;
+                if (brick_blocks(g, k) * (both ? 2 : 1) * 512 > UINT32_MAX) {
+                    ++bad;
+                    printf("FAIL %dx10x10x%d: %lld work items, %lld in plain order\n", x, t,
+                           (long long)(brick_blocks(g, k) * (both ? 2 : 1) * 512), (long long)plain);
+                }
+            }
     printf("cases %d bad %d\n", cases, bad);
     return bad ? 1 : 0;
 }
