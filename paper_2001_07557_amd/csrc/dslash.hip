@@ -735,13 +735,21 @@ constexpr int hop_shape(int prec) {
                                                                      : LQCD_HOP_SHAPE_F16;
 }
 
+// Instances exist for the launches that the rules of hop_launch make.  Links of
+// lattices below 2^17 sites per parity never exceed the Infinity Cache, so the
+// row-parallel and the solver's small-lattice instances have no streamed-link
+// form (NTM bit 1), nor have small ones with a norm (t-region launches, which
+// are small at any size, have none); a build that forces the hints takes the
+// general instance there.
 template <int P, int LK, bool DAG, bool HASY, int NORM, int NTM, bool HALO>
 static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
-    if constexpr (P == LQCD_F64 && DAG && HASY && NORM == 1 && !HALO) {
-        if (a.cg >= CG_RESID) {
+    constexpr bool streamed = (NTM & 2) != 0;
+    if constexpr (DAG && NORM == 1) {
+        // (no other adjoint hop leaves a norm)
+        if constexpr (P == LQCD_F64 && HASY && !HALO) {
 #define LQCD_RESID(PI)                                                                             \
     if (a.cg == CG_RESID + PI) {                                                                   \
-        if (NTM < 2 && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI, (NTM >= 2)><<<grid, 256, a.lds_extra, st>>>(a); \
+        if (!streamed && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI, streamed><<<grid, 256, a.lds_extra, st>>>(a); \
         else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_RESID + PI, true><<<grid, 256, a.lds_extra, st>>>(a); \
         return;                                                                                    \
     }
@@ -750,47 +758,54 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
             LQCD_RESID(LQCD_F16)
 #undef LQCD_RESID
         }
-    }
-    // (small lattices: their links stay cached)
-    if constexpr (P != LQCD_F16 && !DAG && !HALO && NTM < 2 && (HASY ? NORM == 1 : NORM == 0)) {
-        constexpr int role = HASY ? CG_DIR_Y : CG_DIR_IN;
-        if (a.cg == role) {
-            if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role, false><<<grid, 512, 0, st>>>(a);
-            else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, role, false><<<grid, 256, 0, st>>>(a);
-            return;
-        }
-    }
-    if constexpr (DAG && !HASY && !NORM && !HALO) {
-        if (a.cg == CG_PRE) {
-            if constexpr (hop_shape(P) == 8) {
-                if (a.rows) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_PRE, false><<<grid, 512, 0, st>>>(a);
-                else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
-            } else {
-                hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_PRE><<<grid, 256, a.lds_extra, st>>>(a);
-            }
-            return;
-        }
-    }
-    if constexpr (hop_shape(P) == 1) {
-        hop1_kernel<P, LK, DAG, HASY, NORM, NTM, HALO><<<grid, 64, 0, st>>>(a);
-    } else if constexpr (hop_shape(P) == 8) {
-        if constexpr (P == LQCD_F32 && !HASY && !NORM) {
-            if (a.rows) {
-                hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_NONE, false><<<grid, 512, 0, st>>>(a);
-                return;
-            }
-        }
-        if (a.small) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, false><<<grid, 512, 0, st>>>(a);
-        else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, !HALO><<<grid, 512, 0, st>>>(a);
+        return;
     } else {
-        if constexpr (!HALO && LQCD_HOP_TMARCH > 0) {
-            if (a.tseg > 0) {
-                hop4t_kernel<P, LK, DAG, HASY, NORM, NTM><<<grid, 256, a.lds_extra, st>>>(a);
+        if constexpr (P != LQCD_F16 && !DAG && !HALO && !streamed && (HASY ? NORM == 1 : NORM == 0)) {
+            constexpr int role = HASY ? CG_DIR_Y : CG_DIR_IN;
+            if (a.cg == role) {
+                if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role, false><<<grid, 512, 0, st>>>(a);
+                else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, role, false><<<grid, 256, 0, st>>>(a);
                 return;
             }
         }
-        if (a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, false><<<grid, 256, a.lds_extra, st>>>(a);
-        else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, !HALO><<<grid, 256, a.lds_extra, st>>>(a);
+        if constexpr (DAG && !HASY && !NORM && !HALO) {
+            if (a.cg == CG_PRE) {
+                if constexpr (hop_shape(P) == 8) {
+                    if constexpr (!streamed) {
+                        if (a.rows) {
+                            hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_PRE, false><<<grid, 512, 0, st>>>(a);
+                            return;
+                        }
+                    }
+                    hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_PRE><<<grid, 512, 0, st>>>(a);
+                } else {
+                    hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_PRE><<<grid, 256, a.lds_extra, st>>>(a);
+                }
+                return;
+            }
+        }
+        constexpr bool small = HALO || !(streamed && NORM);
+        if constexpr (hop_shape(P) == 1) {
+            hop1_kernel<P, LK, DAG, HASY, NORM, NTM, HALO><<<grid, 64, 0, st>>>(a);
+        } else if constexpr (hop_shape(P) == 8) {
+            if constexpr (P == LQCD_F32 && !HASY && !NORM && !streamed) {
+                if (a.rows) {
+                    hop8_kernel<P, LK, DAG, HASY, NORM, NTM, true, HALO, void, CG_NONE, false><<<grid, 512, 0, st>>>(a);
+                    return;
+                }
+            }
+            if (small && a.small) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, !small><<<grid, 512, 0, st>>>(a);
+            else hop8_kernel<P, LK, DAG, HASY, NORM, NTM, false, HALO, void, CG_NONE, !HALO><<<grid, 512, 0, st>>>(a);
+        } else {
+            if constexpr (!HALO && LQCD_HOP_TMARCH > 0) {
+                if (a.tseg > 0) {
+                    hop4t_kernel<P, LK, DAG, HASY, NORM, NTM><<<grid, 256, a.lds_extra, st>>>(a);
+                    return;
+                }
+            }
+            if (small && a.small) hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, !small><<<grid, 256, a.lds_extra, st>>>(a);
+            else hop4_kernel<P, LK, DAG, HASY, NORM, NTM, HALO, void, CG_NONE, !HALO><<<grid, 256, a.lds_extra, st>>>(a);
+        }
     }
 }
 
@@ -809,19 +824,22 @@ static void launch_nt(const HopArgs &a, dim3 grid, hipStream_t st) {
 
 // The cache hints are template arguments: a run-time choice between two
 // otherwise identical load or store sequences gets merged by the compiler,
-// which then drops the hint.
+// which then drops the hint.  The stores' is the build's, the links' the
+// launch's (LQCD_HOP_STREAM: both the build's).
 template <int P, int LK, bool DAG, bool HASY, int NORM>
 static void launch_shape(const HopArgs &a, dim3 grid, hipStream_t st) {
-    switch (a.stream) {
-        case 0: launch_nt<P, LK, DAG, HASY, NORM, 0>(a, grid, st); break;
-        case 1: launch_nt<P, LK, DAG, HASY, NORM, 1>(a, grid, st); break;
-        case 2: launch_nt<P, LK, DAG, HASY, NORM, 2>(a, grid, st); break;
-        default: launch_nt<P, LK, DAG, HASY, NORM, 3>(a, grid, st); break;
+    constexpr int hint = LQCD_HOP_STREAM >= 0 ? LQCD_HOP_STREAM & 3 : OUT_NT ? 1 : 0;
+    if constexpr (LQCD_HOP_STREAM < 0 && LQCD_LINK_NT) {
+        if (a.stream & 2) {
+            launch_nt<P, LK, DAG, HASY, NORM, hint | 2>(a, grid, st);
+            return;
+        }
     }
+    launch_nt<P, LK, DAG, HASY, NORM, hint>(a, grid, st);
 }
 
-// norm: 0 none, 1 |out|^2 block partials, 2 CG update (needs the y term; the
-// solver applies it on the adjoint hop only)
+// norm: 0 none, 1 |out|^2 block partials (with a y term), 2 CG update (needs
+// the y term; the solver applies it on the adjoint hop only)
 template <int P, int LK, bool DAG>
 static void launch_p(const HopArgs &a, bool hasy, int norm, dim3 grid, hipStream_t st) {
     if (hasy) {
@@ -833,8 +851,7 @@ static void launch_p(const HopArgs &a, bool hasy, int norm, dim3 grid, hipStream
             launch_shape<P, LK, DAG, true, 0>(a, grid, st);
         }
     } else {
-        if (norm == 1) launch_shape<P, LK, DAG, false, 1>(a, grid, st);
-        else launch_shape<P, LK, DAG, false, 0>(a, grid, st);
+        launch_shape<P, LK, DAG, false, 0>(a, grid, st);
     }
 }
 
@@ -935,6 +952,8 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     const bool hasy = a.y[0] != nullptr || a.y[1] != nullptr;
     const int norm = a.cg == CG_UPDATE ? 2 : a.partial != nullptr ? 1 : 0;
     const bool dir = a.cg == CG_DIR_IN || a.cg == CG_DIR_Y;
+    // (of the hops that leave a norm, the adjoint ones are those of CG_RESID)
+    if (norm == 1 && (!hasy || (dag && a.cg < CG_RESID))) return LQCD_EINVAL;
     if (dir && (prec == LQCD_F16 || dag || !a.sums || !a.sc || !a.p_old || (a.stream & 2))) return LQCD_EINVAL;
     if (a.cg == CG_DIR_IN && (hasy || norm)) return LQCD_EINVAL;
     if (a.cg == CG_DIR_Y && (!hasy || norm != 1 || !a.p_new || !a.x || a.p_new == a.p_old)) return LQCD_EINVAL;
