@@ -548,6 +548,8 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = {0, 0};
     double nrm[1] = {0.0};
+    double alpha = 0.0;
+    if constexpr (NORM == 2) alpha = cg_alpha_of(a);  // (a sum over the whole wave)
     if (active) {
         constexpr bool LNT = (NTM & 2) != 0;
         hop_direction<0, P, LK, DAG, LNT>(g, a.in[p], a.U, p, s, c, acc);
@@ -561,7 +563,7 @@ __global__ __launch_bounds__(64) void hop1_kernel(HopArgs a) {
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[k] = acc[k] + d[k];
         load_y<P, HASY, false>(a, p, s, d);
-        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, d, acc, NORM == 2 ? cg_alpha_of(a) : 0.0);
+        nrm[0] = hop_epilogue<P, HASY, NORM, (NTM & 1) != 0>(a, p, s, d, acc, alpha);
     }
     if constexpr (NORM) {
         const double t = wave_sum(nrm[0]);
