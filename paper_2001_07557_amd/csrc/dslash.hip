@@ -762,7 +762,7 @@ static void launch_halo(const HopArgs &a, dim3 grid, hipStream_t st) {
         }
         return;
     } else {
-        if constexpr (P != LQCD_F16 && !DAG && !HALO && !streamed && (HASY ? NORM == 1 : NORM == 0)) {
+        if constexpr (P != LQCD_F16 && !DAG && !HALO && (!streamed || LQCD_HOP_STREAM >= 0) && (HASY ? NORM == 1 : NORM == 0)) {
             constexpr int role = HASY ? CG_DIR_Y : CG_DIR_IN;
             if (a.cg == role) {
                 if constexpr (hop_shape(P) == 8) hop8_kernel<P, LK, DAG, HASY, NORM, NTM, !HASY && P == LQCD_F32, HALO, void, role, false><<<grid, 512, 0, st>>>(a);
@@ -960,7 +960,9 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     const bool dir = a.cg == CG_DIR_IN || a.cg == CG_DIR_Y;
     // (of the hops that leave a norm, the adjoint ones are those of CG_RESID)
     if (norm == 1 && (!hasy || (dag && a.cg < CG_RESID))) return LQCD_EINVAL;
-    if (dir && (prec == LQCD_F16 || dag || !a.sums || !a.sc || !a.p_old || (a.stream & 2))) return LQCD_EINVAL;
+    if (dir && (prec == LQCD_F16 || dag || !a.sums || !a.sc || !a.p_old ||
+                ((a.stream & 2) && LQCD_HOP_STREAM < 0)))
+        return LQCD_EINVAL;
     if (a.cg == CG_DIR_IN && (hasy || norm)) return LQCD_EINVAL;
     if (a.cg == CG_DIR_Y && (!hasy || norm != 1 || !a.p_new || !a.x || a.p_new == a.p_old)) return LQCD_EINVAL;
     if ((a.cg == CG_PRE || a.cg == CG_UPDATE) && (!dag || !a.sums || !a.sc)) return LQCD_EINVAL;
