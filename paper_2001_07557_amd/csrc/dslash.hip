@@ -941,10 +941,11 @@ int hop_launch(const HopArgs &a0, int prec, int link, bool dag, int nparity, hip
     a.small = short_launch || (prec == LQCD_F16 && !a.rev && a.brick.lz != 0);
     dim3 grid((unsigned)(a.bpp * nparity));
     // t-march launches (4-way shape, one parity, whole lattice, whole tiles
-    // per t-slice in a multiple of 8 columns): one block per column and
-    // segment of tseg slices
+    // per t-slice in a multiple of 8 columns; the solver's other roles are
+    // those of the 4-way form): one block per column and segment of tseg slices
     a.tseg = 0;
     if (LQCD_HOP_TMARCH > 0 && hop_shape(prec) == 4 && nparity == 1 && region < 0 &&
+        (a.cg == CG_NONE || a.cg == CG_UPDATE) &&
         a.g.vh >= ((int64_t)1 << LQCD_HOP_TMARCH_MIN_LOG2) && a.g.st % TILE == 0 &&
         (a.g.st / TILE) % 8 == 0) {
         a.tseg = LQCD_HOP_TMARCH;
