@@ -7,11 +7,15 @@
 
 namespace lqcd {
 
-constexpr int MAIL_SLOTS = 64;
+// (0, for a test build: every call copies its numbers)
+#ifndef LQCD_MAIL_SLOTS
+#define LQCD_MAIL_SLOTS 64
+#endif
+constexpr int MAIL_SLOTS = LQCD_MAIL_SLOTS;
 static std::mutex mail_mutex;
 static Mail *mail_page = nullptr;
 static uint64_t mail_used = 0;  // a bit per slot
-static_assert(MAIL_SLOTS * sizeof(Mail) == 4096, "one page");
+static_assert(MAIL_SLOTS <= 64 && MAIL_SLOTS * sizeof(Mail) <= 4096, "one page, a bit per slot");
 
 void MailSlot::open(hipStream_t st) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -19,7 +23,7 @@ void MailSlot::open(hipStream_t st) {
         (void)hipGetLastError();
         return;
     }
-    if (status != hipStreamCaptureStatusNone) return;
+    if (status != hipStreamCaptureStatusNone || MAIL_SLOTS == 0) return;
     std::lock_guard<std::mutex> lock(mail_mutex);
     if (!mail_page) {
         // (allowed while another thread captures a graph)
