@@ -292,11 +292,16 @@ static int read_gap(int left) {
 // reading the residual every iteration near the end would otherwise add an
 // FP64 update a few iterations before the last one (at 32^4 FP32 inner:
 // three updates instead of two).  It is put off only until the inner
-// residual has fallen DRIFT_HARD (squared: 1e-4, a further factor 100, about
-// the most that reads every ten iterations let it drift) below the drift
-// threshold: without that bound an 8^4 FP32-inner solve to 1e-12, whose
-// recurrence keeps predicting the end, took 300 iterations instead of
-// under 200.  binary16 inner solves, whose drift rule fires at every
+// residual is found, at a read, to have fallen DRIFT_HARD (squared: 1e-4, a
+// further factor 100) below the drift threshold: without that bound an 8^4
+// FP32-inner solve to 1e-12, whose recurrence keeps predicting the end, took
+// 300 iterations instead of under 200 (with a threshold of 1e-3).  With the
+// threshold of 1e-4 the bound is 1e-6, and 1e-2 in its place (1e-5) changes
+// no solve by more than one update: 50 systems of 36 to 1400 FP64 iterations, to
+// 1e-10 and 1e-12, take 0 to 9% more iterations with FP32 inner than FP64 either
+// way (Haar links 8^4 kappa 0.24 1403 -> 1444 and 1634 -> 1669; kappa 0.22 267
+// -> 276 and 321 -> 329; 12^4 spread by 0.4 201 -> 206 and 240 -> 254), and so
+// with a threshold of 1e-3, at one or two updates more.  binary16 inner solves, whose drift rule fires at every
 // tenfold fall, take every drift update (put off, the 32^4 solve needed 55
 // iterations instead of 46).
 constexpr int DRIFT_DEFER = CHECK_EVERY;

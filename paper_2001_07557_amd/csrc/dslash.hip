@@ -50,14 +50,17 @@ namespace lqcd {
 #ifndef LQCD_HOP_PAIRED
 #define LQCD_HOP_PAIRED 1
 #endif
-// Blocks in flight of the FP64 4-way kernel.  With ~120 VGPRs and 36 KB of
-// LDS four blocks fit a CU, and an XCD's 32 CUs then keep 128 tiles in flight,
-// more than one t-slice of its z-slab: the three input t-slices the brick
-// order relies on no longer fit its 4 MB L2 beside them.  Even-odd launches
-// from V/2 >= 2^17 and both-parity launches from 2^15 add dynamic LDS that
-// leaves three blocks per CU.  Measured (us, four -> three -> two blocks per
-// CU): full-lattice M 24^4 FP64-18 81.4 -> 78.5 -> 80.6, FP64-12 67.8 -> 67.1
-// -> 71.2; 32^4 FP64-18 238.5 -> 228.7 -> 236.5, FP64-12 196.2 -> 193.4 ->
+// Blocks in flight of the FP64 4-way kernel.  By its 36 KB of LDS four blocks
+// fit a CU, and by registers where an instance has at most 128 VGPRs: 114-120
+// without a y term and on small lattices, 126 for the large adjoint with one;
+// the large forward ones that read y early have 130-132, a canonical FP64
+// result 132, the CG update 148, and fit three whatever the LDS.  With four an
+// XCD's 32 CUs keep 128 tiles in flight, more than one t-slice of its z-slab:
+// the three input t-slices the brick order relies on no longer fit its 4 MB L2
+// beside them.  Even-odd launches from V/2 >= 2^17 and both-parity launches
+// from 2^15 add dynamic LDS that leaves three blocks per CU.  Measured (us, four
+// -> three -> two blocks per CU, y read late, 120 VGPRs): full-lattice M 24^4
+// FP64-18 81.4 -> 78.5 -> 80.6, FP64-12 67.8 -> 67.1 -> 71.2; 32^4 FP64-18 238.5 -> 228.7 -> 236.5, FP64-12 196.2 -> 193.4 ->
 // 209.5; 48^3x96 FP64-18 2470 -> 2397 -> 2445, FP64-12 2016 -> 1996 -> 2156;
 // 16^3x32 FP64-18 33.8 -> 32.6; Mhat 32^4 FP64-18 285.1 -> 283.7, 28^4
 // FP64-18 175.6 -> 173.5, 38^3x40 FP64-12 -> 512 -> 527, 48^3x96 FP64-12
@@ -75,7 +78,8 @@ constexpr int64_t F64_SLAB_TWO_BYTES = (int64_t)3 << 20;
 #define LQCD_HOP_F64_LDS_MIN_LOG2 17
 #endif
 // (t-region launches, short as they are, only from 2^20: 32^3x8 FP64-18 face
-// pack, interior and boundary 49.6 us with three blocks, 48.9 with four)
+// pack, interior and boundary 49.6 us with three blocks, 48.9 with four; the
+// forward ones with streamed links and a y term fit three by their registers)
 #ifndef LQCD_HOP_F64_REGION_LDS_MIN_LOG2
 #define LQCD_HOP_F64_REGION_LDS_MIN_LOG2 20
 #endif

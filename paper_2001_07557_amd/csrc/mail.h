@@ -2,7 +2,8 @@
 // pinned host memory and the host, which has nothing else to do meanwhile,
 // watches the slot's count.  An 8-byte copy to pageable memory is a launch of
 // its own and a wait for its completion, 20-25 us in which the GPU idles; a
-// posted value arrives 2-3 us after the kernel's end.
+// posted value arrives 2-3 us after the kernel's end.  (A reduction, which
+// synchronises its stream in any case, saves the copy alone.)
 //
 // One 4 KiB page per process, allocated at the first use and kept (64 slots,
 // each given out to one call at a time and handed back at its end); a call
