@@ -38,10 +38,12 @@ public:
     // waits for the post numbered last by next(), made by a kernel on the
     // slot's stream: watched for some milliseconds, then by synchronising
     int wait(double *out, int nv);
-    // the post numbered last, the stream having been synchronised
-    int take(double *out, int nv) const;
+    // the same, and the stream is synchronised
+    int finish(double *out, int nv);
 
 private:
+    int take(double *out, int nv) const;
+
     Mail *m_ = nullptr;
     uint64_t n_ = 0;
     int slot_ = -1;

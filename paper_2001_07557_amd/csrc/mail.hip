@@ -85,6 +85,26 @@ int MailSlot::wait(double *out, int nv) {
     return take(out, nv);
 }
 
+// An event behind the post is waited for in the stream's place: once five or
+// six launches have gone before it, hipStreamSynchronize returns 30 us after
+// the last one has ended, an event 6 us after (a reduction behind eight shifts
+// of 8^4, whole sequence: 83 -> 53 us; 48-54 without either).
+int MailSlot::finish(double *out, int nv) {
+    hipEvent_t ev;
+    const bool have = hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+    const bool recorded = have && hipEventRecord(ev, st_) == hipSuccess;
+    if (!recorded) (void)hipGetLastError();
+    const int rc = wait(out, nv);
+    hipError_t e = hipSuccess;
+    if (!rc) e = recorded ? hipEventSynchronize(ev) : hipStreamSynchronize(st_);
+    if (have) (void)hipEventDestroy(ev);
+    if (e != hipSuccess) {
+        set_hip_error(e);
+        return LQCD_EHIP;
+    }
+    return rc;
+}
+
 int MailSlot::take(double *out, int nv) const {
     if (__atomic_load_n(&m_->count, __ATOMIC_ACQUIRE) != n_) {
         set_hip_error(hipErrorUnknown);

@@ -19,8 +19,8 @@ struct Post {
     double v[2];
 };
 std::deque<Post> queue;   // enqueued, not yet run
-bool drain_fails = false;
-int drains = 0;
+bool drain_fails = false, record_fails = false;
+int drains = 0, events = 0;
 
 void enqueue(lqcd::MailSlot &s, double a, double b) { queue.push_back({s.get(), s.next(), {a, b}}); }
 void run_all() {
@@ -57,6 +57,16 @@ hipError_t hipStreamSynchronize(hipStream_t) {
     if (drain_fails) return hipErrorUnknown;
     run_all();
     return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    *e = nullptr;
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return record_fails ? hipErrorUnknown : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) {
+    ++events;
+    return hipStreamSynchronize(nullptr);
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 }
@@ -117,6 +127,21 @@ int main() {
         const double cpu = (double)(clock() - t0) / CLOCKS_PER_SEC;
         check(rc == LQCD_OK && out[0] == 3.0 && out[1] == 4.0, "a late post is received");
         check(drains > was && cpu < 1.0, "the host stops watching after a while");
+    }
+    // a result that is waited for together with its stream, by an event or
+    // without one
+    for (bool fails : {false, true}) {
+        record_fails = fails;
+        MailSlot a;
+        a.open(nullptr);
+        enqueue(a, 7.0, 8.0);
+        run_all();
+        double out[2];
+        const int was = drains, ev = events;
+        check(a.finish(out, 2) == LQCD_OK && out[0] == 7.0 && out[1] == 8.0 && drains > was &&
+                  events == ev + !fails,
+              "a finished call has drained its stream");
+        record_fails = false;
     }
     // a stream that fails, and one that ends without a post
     {
