@@ -35,20 +35,20 @@ from . import lqcd as L
 # the 288 is one such application, or four at 24^4.
 KEEP_BYTES = 1 << 30
 _keep_lock = threading.Lock()
-_held = collections.Counter()      # device -> bytes given out
-_returned = collections.deque()    # shares given back, not yet counted
+_held = collections.defaultdict(int)  # device -> bytes given out
+_returned = collections.deque()       # shares given back, not yet counted
 
 
 class _Share:
-    """A part of the bound, given back when the last buffer that carries it is
-    freed (in whichever thread that happens, so without the lock)."""
-    __slots__ = ("device", "bytes")
+    """A part of the bound, given back when the buffer that carries it is freed
+    (in whichever thread that happens, so without the lock)."""
+    __slots__ = ("part",)
 
-    def __init__(self, device, nbytes):
-        self.device, self.bytes = device, nbytes
+    def __init__(self, part):
+        self.part = part
 
-    def __del__(self, back=_returned):
-        back.append((self.device, self.bytes))
+    def __del__(self, back=_returned.append):
+        back(self.part)
 
 
 def _take_share(device, nbytes):
@@ -57,10 +57,11 @@ def _take_share(device, nbytes):
         while _returned:
             d, n = _returned.popleft()
             _held[d] -= n
-        if _held[device] + nbytes > KEEP_BYTES:
+        held = _held[device] + nbytes
+        if held > KEEP_BYTES:
             return None
-        _held[device] += nbytes
-        return _Share(device, nbytes)
+        _held[device] = held
+    return _Share((device, nbytes))
 
 
 class WilsonMatrix(torch.autograd.Function):
@@ -71,11 +72,13 @@ class WilsonMatrix(torch.autograd.Function):
         Uf = L.pack_gauge(lattice, U.contiguous(), prec, link)
         pf = L.pack_spinor(lattice, psi.contiguous(), prec, L.FULL)
         # psi and U themselves carry the check that nobody has changed them
-        keep = [Uf.buf, pf.buf] if ctx.needs_input_grad[1] else [Uf.buf]
-        share = _take_share(psi.device, sum(b.numel() for b in keep))
-        for b in keep:
-            b.share = share
-        ctx.save_for_backward(psi, U, *(keep if share is not None else ()))
+        with_psi = ctx.needs_input_grad[1]
+        share = _take_share(psi.get_device(), Uf.buf.numel() + (pf.buf.numel() if with_psi else 0))
+        if share is None:
+            ctx.save_for_backward(psi, U)
+        else:
+            Uf.buf.share = share  # (the two buffers are freed together)
+            ctx.save_for_backward(psi, U, Uf.buf, pf.buf if with_psi else None)
         ctx.cfg = (kappa, lattice, prec, link, link_grad)
         return L.wilson_canonical(pf, Uf, kappa, psi.dtype)
 
