@@ -70,6 +70,10 @@ namespace lqcd {
 // halves (144 bytes per site of a t-slice and slab) overflow the L2: 38^3x40
 // 575 -> 536 -> 522, 46^3x50 1318 -> 1221 -> 1180; at 28^4 (1.6 MB) three are
 // ahead, 147.0 -> 140.5 -> 144.4.
+// With y read early the limit acts on the adjoint, the small instances and the
+// launches that want two: M^dag FP64-18 32^4 236.6 -> 226.9 us and 1433 -> 1256
+// MB fetched, 28^4 146.9 -> 140.1 and 923 -> 841, 38^3x40 (two) 579.7 -> 507.1
+// and 4151 -> 3333; the large forward M has the same times and bytes without it.
 // binary16 storage (also 4-way) loses 8 points with two and keeps what fits.
 // LQCD_HOP_EXTRA_LDS forces a value for every 4-way launch (ablations).
 constexpr uint32_t F64_LDS_THREE = 6144, F64_LDS_TWO = 18432;

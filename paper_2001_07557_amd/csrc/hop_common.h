@@ -115,7 +115,9 @@ __device__ __forceinline__ void hop_fence(cplx<T> acc[N]) {
 // Measured (us, plain order -> slabs, two runs each within 0.5%): Mhat 28^4
 // FP32-12 75.8 -> 68.8, 30^4 FP32-18 124.1 -> 112.7, 46^3x50 FP32-12 587 ->
 // 546, binary16 319 -> 300; full-lattice M 28^4 FP64-18 160.3 -> 142.7,
-// 46^3x50 FP64-18 1379 -> 1159, 18^2x42x40 FP64-12 121.1 -> 116.  Slabs half
+// 46^3x50 FP64-18 1379 -> 1159, 18^2x42x40 FP64-12 121.1 -> 116 (fetched: 612 ->
+// 418 MB; Mhat 28^4 FP32-12 444 -> 364 in its two hops; the 18-real FP64 M as
+// much, at three blocks per CU instead of the two of its plain order).  Slabs half
 // as thick, two per XCD, lose 5-8% (the planes at every edge are read again).
 __host__ __device__ __forceinline__ uint32_t slab_tile(const Geom &g, uint32_t t, uint32_t j) {
     const uint32_t st = (uint32_t)g.st;
