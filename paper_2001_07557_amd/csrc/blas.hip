@@ -10,6 +10,7 @@
 #include "lqcd_internal.h"
 #include "reduce.h"
 #include "blas.h"
+#include "grid.h"
 #include "mail.h"
 
 namespace lqcd {
@@ -155,16 +156,9 @@ __global__ __launch_bounds__(FIN_BLOCK) void finalize_k(const double *partial, i
     }
 }
 
-// Kernels of one 16-byte word per thread.  A launch counts its work items in
-// 32 bits per dimension and drops what is beyond (an FP64 full field of V >=
-// 357.9M sites, 69 GB, has more words), so the blocks beyond 2^23 go into y.
-static dim3 word_grid(int64_t n) {
-    const int64_t blocks = (n + RED_BLOCK - 1) / RED_BLOCK, row = (int64_t)1 << 23;
-    return dim3((unsigned)(blocks < row ? blocks : row), (unsigned)((blocks + row - 1) / row));
-}
-__device__ __forceinline__ int64_t word_index() {
-    return ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * RED_BLOCK + threadIdx.x;
-}
+// Kernels of one 16-byte word per thread.
+static dim3 word_grid(int64_t n) { return block_grid((n + RED_BLOCK - 1) / RED_BLOCK); }
+__device__ __forceinline__ int64_t word_index() { return block_index() * RED_BLOCK + threadIdx.x; }
 
 // y = a x + b y on 16-byte words (FP64, FP32): one word per thread, as the
 // copy below (a thread per site: 118 us at 32^4 FP64, full field; now 105, 5.7

@@ -15,6 +15,7 @@
 
 #include "lqcd_internal.h"
 #include "hop_common.h"
+#include "grid.h"
 
 namespace lqcd {
 
@@ -101,7 +102,7 @@ template <int P>
 __global__ __launch_bounds__(256) void cshift_words_k(Geom g, char *out, const char *in, int64_t hb,
                                                       int mu, int fwd, int64_t wpp) {
     constexpr int NW = P == LQCD_F64 ? 12 : P == LQCD_F32 ? 6 : 4;
-    const int64_t gw = xcd_block(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int64_t gw = xcd_block((uint32_t)block_index(), block_count()) * 4 + (threadIdx.x >> 6);
     if (gw >= 2 * wpp) return;
     const int p = gw >= wpp ? 1 : 0;
     const int64_t lw = gw - p * wpp;
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(256) void cshift_words_k(Geom g, char *out, const c
 template <typename E>
 __global__ __launch_bounds__(256) void split_rotate_wave_k(E *out, const E *in, int64_t n,
                                                            int vl, int w, int r) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_index() * 256 + threadIdx.x;
     const int lane = threadIdx.x & 63;
     // every lane takes part in the exchange; lanes past n carry a dummy value
     E x = i < n ? in[i] : E{};
@@ -150,7 +151,8 @@ constexpr int ROT_BLOCK = 256, ROT_PER = 4;
 template <typename E>
 __global__ __launch_bounds__(ROT_BLOCK) void split_rotate_gather_k(E *out, const E *in, int64_t n,
                                                                    FastDiv vl, FastDiv w, int r) {
-    const int64_t b0 = (int64_t)blockIdx.x * (ROT_BLOCK * ROT_PER);
+    const int64_t b0 = block_index() * (ROT_BLOCK * ROT_PER);
+    if (b0 >= n) return;
     const uint32_t off = (uint32_t)(b0 % vl.d);  // the block starts inside a vector
     const int left = n - b0 < ROT_BLOCK * ROT_PER ? (int)(n - b0) : ROT_BLOCK * ROT_PER;
     const E *src = in + b0;
@@ -200,7 +202,7 @@ extern "C" int lqcd_cshift(const lqcd_geom_t *gg, void *out, const void *in, int
     // 67.3% of 8 TB/s, HIP events, two runs each), FP32 unchanged
     const int nw = prec == LQCD_F64 ? 12 : prec == LQCD_F32 ? 6 : 4;
     const int64_t wpp = g.ntiles * nw;  // waves per parity
-    dim3 grid((unsigned)((2 * wpp + 3) / 4)), block(256);
+    const dim3 grid = block_grid((2 * wpp + 3) / 4), block(256);
     if (prec == LQCD_F64) cshift_words_k<LQCD_F64><<<grid, block, 0, st>>>(g, (char *)out, (const char *)in, hb, mu, fwd, wpp);
     else if (prec == LQCD_F32) cshift_words_k<LQCD_F32><<<grid, block, 0, st>>>(g, (char *)out, (const char *)in, hb, mu, fwd, wpp);
     else cshift_words_k<LQCD_F16><<<grid, block, 0, st>>>(g, (char *)out, (const char *)in, hb, mu, fwd, wpp);
@@ -218,10 +220,10 @@ extern "C" int lqcd_split_rotate(void *out, const void *in, int64_t nvec, int vl
     if ((n + 255) / 256 > 0x7fffffff) return LQCD_EINVAL;
     const int w = vl / s;
     const int rr = ((r % w) + w) % w;
-    dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    const dim3 grid = block_grid((n + 255) / 256), block(256);
     hipStream_t st = (hipStream_t)stream;
     const bool in_wave = 64 % vl == 0;
-    const dim3 gather((unsigned)((n + ROT_BLOCK * ROT_PER - 1) / (ROT_BLOCK * ROT_PER)));
+    const dim3 gather = block_grid((n + ROT_BLOCK * ROT_PER - 1) / (ROT_BLOCK * ROT_PER));
     const FastDiv dv = make_fastdiv((uint32_t)vl), dw = make_fastdiv((uint32_t)w);
     if (elem_bytes == 8) {
         if (in_wave) split_rotate_wave_k<double><<<grid, block, 0, st>>>((double *)out, (const double *)in, n, vl, w, rr);
