@@ -591,7 +591,9 @@ extern "C" int lqcd_cg_solve(const lqcd_geom_t *gg, void *x_e, const void *b_e, 
     if (inner_prec == LQCD_F64) rc = s.run<LQCD_F64>((char *)x_e, (const char *)b_e, tol, maxiter, reliable_every, st);
     else if (inner_prec == LQCD_F32) rc = s.run<LQCD_F32>((char *)x_e, (const char *)b_e, tol, maxiter, reliable_every, st);
     else rc = s.run<LQCD_F16>((char *)x_e, (const char *)b_e, tol, maxiter, reliable_every, st);
-    const hipError_t e = hipStreamSynchronize(s.st);
+    // (a solve that failed may have failed because its stream is captured,
+    // where an event would become part of the graph)
+    const hipError_t e = rc == LQCD_OK ? drain_stream(s.st) : hipStreamSynchronize(s.st);
     if (e != hipSuccess && rc == LQCD_OK) {
         set_hip_error(e);
         rc = LQCD_EHIP;

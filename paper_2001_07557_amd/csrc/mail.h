@@ -50,6 +50,9 @@ private:
     hipStream_t st_ = nullptr;
 };
 
+// Synchronises the stream, by an event (mail.hip).
+hipError_t drain_stream(hipStream_t st);
+
 // One thread of the grid posts v[0..1].
 __device__ __forceinline__ void mail_post(Mail *m, uint64_t count, double a, double b) {
     __hip_atomic_store(&m->v[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -143,6 +143,13 @@ int main() {
               "a finished call has drained its stream");
         record_fails = false;
     }
+    for (bool fails : {false, true}) {
+        record_fails = fails;
+        const int was = drains, ev = events;
+        check(drain_stream(nullptr) == hipSuccess && drains == was + 1 && events == ev + !fails,
+              "a stream is drained, by an event or without one");
+        record_fails = false;
+    }
     // a stream that fails, and one that ends without a post
     {
         MailSlot a;
